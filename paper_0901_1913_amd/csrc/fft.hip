@@ -26,6 +26,8 @@
 // point order, with the same kernel argument (cell - position, exact) as the
 // standalone spreading: the cell values, and so every later result, are the
 // same bit for bit.
+#include <type_traits>
+
 #include "fchi2_internal.h"
 #include "launch.h"
 #include "fft_tile.h"
@@ -36,57 +38,75 @@ namespace {
 
 template <typename S, int LOGN, int LOGT>
 hipError_t launch_one(const FftPassArgs& a, const void* in, void* out, const Moments* mom,
-                      const Geom& g, const void* tws, const void* twsm, int n_curves,
-                      int64_t ncols, hipStream_t st) {
+                      const Geom& g, const void* tws, int n_curves, int64_t ncols,
+                      hipStream_t st) {
   dim3 grid((unsigned)(ncols >> LOGT), (unsigned)g.P, (unsigned)n_curves);
   dim3 blk(((1 << LOGN) << LOGT) / kEPT);
-  if (a.fused) {
-    if (a.kind != PASS_FIRST || a.mode != MODE_FWD || g.band || !a.t || !a.x || !a.sigma ||
+  auto launch = [&](auto fused, auto kind) {
+    constexpr bool FZ = decltype(fused)::value;
+    constexpr int KD = decltype(kind)::value;
+    hipLaunchKernelGGL((k_fft_pass<S, LOGN, LOGT, FZ, KD>), grid, blk, 0, st, a,
+                       (const cplx<S>*)in, (cplx<S>*)out, mom, g, (const C*)tws);
+  };
+  if constexpr (LOGT == 0) {
+    if (a.fused || a.kind != PASS_SINGLE) return hipErrorInvalidValue;
+    launch(std::false_type{}, std::integral_constant<int, TILE_SINGLE>{});
+  } else if (a.fused) {
+    if (a.kind != PASS_FIRST || a.mode != MODE_FWD || g.band || (a.np == 2 && !a.tw_tile) || !a.t || !a.x || !a.sigma ||
         !a.tb || (1 << a.tb_log) < g.w + 3)
       return hipErrorInvalidValue;
-    if constexpr (LOGT >= 1)
-      hipLaunchKernelGGL((k_fft_pass<S, LOGN, LOGT, true>), grid, blk, 0, st, a,
-                         (const cplx<S>*)in, (cplx<S>*)out, mom, g, (const C*)tws,
-                         (const C*)twsm);
+    if (a.np == 2)
+      launch(std::true_type{}, std::integral_constant<int, TILE_FIRST2>{});
     else
-      return hipErrorInvalidValue;
+      launch(std::true_type{}, std::integral_constant<int, TILE_FIRST>{});
+  } else if (a.kind == PASS_FIRST) {
+    if (a.np == 2 && !a.tw_tile) return hipErrorInvalidValue;
+    if (a.np == 2)
+      launch(std::false_type{}, std::integral_constant<int, TILE_FIRST2>{});
+    else
+      launch(std::false_type{}, std::integral_constant<int, TILE_FIRST>{});
+  } else if (a.kind == PASS_MID) {
+    launch(std::false_type{}, std::integral_constant<int, TILE_MID>{});
+  } else if (a.kind == PASS_LAST && a.mode == MODE_FWD && !g.band) {
+    launch(std::false_type{}, std::integral_constant<int, TILE_LAST>{});
+  } else if (a.kind == PASS_LAST) {
+    launch(std::false_type{}, std::integral_constant<int, TILE_LAST_ANY>{});
   } else {
-    hipLaunchKernelGGL((k_fft_pass<S, LOGN, LOGT, false>), grid, blk, 0, st, a,
-                       (const cplx<S>*)in, (cplx<S>*)out, mom, g, (const C*)tws, (const C*)twsm);
+    return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 template <typename S>
 hipError_t dispatch(const FftPassArgs& a, int logn, int logt, const void* in, void* out,
-                    const Moments* mom, const Geom& g, const void* tws, const void* twsm,
-                    int n_curves, int64_t ncols, hipStream_t st) {
+                    const Moments* mom, const Geom& g, const void* tws, int n_curves,
+                    int64_t ncols, hipStream_t st) {
   if (logt == 0) {
-    if (logn == 12) return launch_one<S, 12, 0>(a, in, out, mom, g, tws, twsm, n_curves, ncols, st);
+    if (logn == 12) return launch_one<S, 12, 0>(a, in, out, mom, g, tws, n_curves, ncols, st);
     if constexpr (tile_log_max<S>() == 13)
-      if (logn == 13) return launch_one<S, 13, 0>(a, in, out, mom, g, tws, twsm, n_curves, ncols, st);
+      if (logn == 13) return launch_one<S, 13, 0>(a, in, out, mom, g, tws, n_curves, ncols, st);
     return hipErrorInvalidValue;
   }
   if (logn + logt == 12) {
     switch (logn) {
-      case 4: return launch_one<S, 4, 8>(a, in, out, mom, g, tws, twsm, n_curves, ncols, st);
-      case 5: return launch_one<S, 5, 7>(a, in, out, mom, g, tws, twsm, n_curves, ncols, st);
-      case 6: return launch_one<S, 6, 6>(a, in, out, mom, g, tws, twsm, n_curves, ncols, st);
-      case 7: return launch_one<S, 7, 5>(a, in, out, mom, g, tws, twsm, n_curves, ncols, st);
-      case 8: return launch_one<S, 8, 4>(a, in, out, mom, g, tws, twsm, n_curves, ncols, st);
-      case 9: return launch_one<S, 9, 3>(a, in, out, mom, g, tws, twsm, n_curves, ncols, st);
+      case 4: return launch_one<S, 4, 8>(a, in, out, mom, g, tws, n_curves, ncols, st);
+      case 5: return launch_one<S, 5, 7>(a, in, out, mom, g, tws, n_curves, ncols, st);
+      case 6: return launch_one<S, 6, 6>(a, in, out, mom, g, tws, n_curves, ncols, st);
+      case 7: return launch_one<S, 7, 5>(a, in, out, mom, g, tws, n_curves, ncols, st);
+      case 8: return launch_one<S, 8, 4>(a, in, out, mom, g, tws, n_curves, ncols, st);
+      case 9: return launch_one<S, 9, 3>(a, in, out, mom, g, tws, n_curves, ncols, st);
       default: return hipErrorInvalidValue;
     }
   }
   if constexpr (tile_log_max<S>() == 13) {
     if (logn + logt == 13) {
       switch (logn) {
-        case 4: return launch_one<S, 4, 9>(a, in, out, mom, g, tws, twsm, n_curves, ncols, st);
-        case 5: return launch_one<S, 5, 8>(a, in, out, mom, g, tws, twsm, n_curves, ncols, st);
-        case 6: return launch_one<S, 6, 7>(a, in, out, mom, g, tws, twsm, n_curves, ncols, st);
-        case 7: return launch_one<S, 7, 6>(a, in, out, mom, g, tws, twsm, n_curves, ncols, st);
-        case 8: return launch_one<S, 8, 5>(a, in, out, mom, g, tws, twsm, n_curves, ncols, st);
-        case 9: return launch_one<S, 9, 4>(a, in, out, mom, g, tws, twsm, n_curves, ncols, st);
+        case 4: return launch_one<S, 4, 9>(a, in, out, mom, g, tws, n_curves, ncols, st);
+        case 5: return launch_one<S, 5, 8>(a, in, out, mom, g, tws, n_curves, ncols, st);
+        case 6: return launch_one<S, 6, 7>(a, in, out, mom, g, tws, n_curves, ncols, st);
+        case 7: return launch_one<S, 7, 6>(a, in, out, mom, g, tws, n_curves, ncols, st);
+        case 8: return launch_one<S, 8, 5>(a, in, out, mom, g, tws, n_curves, ncols, st);
+        case 9: return launch_one<S, 9, 4>(a, in, out, mom, g, tws, n_curves, ncols, st);
         default: return hipErrorInvalidValue;
       }
     }
@@ -100,9 +120,16 @@ int fft_tile_log(bool fp64) { return fp64 ? tile_log_max<double>() : tile_log_ma
 
 hipError_t launch_fft_pass(bool fp64, const FftPassArgs& a, int logn, int logt, const void* in,
                            void* out, const Moments* mom, const Geom& g, const void* tws,
-                           const void* twsm, int n_curves, int64_t ncols, hipStream_t st) {
-  if (fp64) return dispatch<double>(a, logn, logt, in, out, mom, g, tws, twsm, n_curves, ncols, st);
-  return dispatch<float>(a, logn, logt, in, out, mom, g, tws, twsm, n_curves, ncols, st);
+                           int n_curves, int64_t ncols, hipStream_t st) {
+  if (fp64) return dispatch<double>(a, logn, logt, in, out, mom, g, tws, n_curves, ncols, st);
+  return dispatch<float>(a, logn, logt, in, out, mom, g, tws, n_curves, ncols, st);
+}
+
+hipError_t launch_tile_tw(const void* small, int logn, int logt, void* out, hipStream_t st) {
+  const unsigned n = 1u << (logn + logt);
+  hipLaunchKernelGGL(k_tile_tw, dim3((n + 255) / 256), dim3(256), 0, st, (const C*)small, logn,
+                     logt, (C*)out);
+  return hipGetLastError();
 }
 
 }  // namespace fchi2

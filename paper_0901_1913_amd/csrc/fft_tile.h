@@ -21,25 +21,43 @@ constexpr double kS16[16] = {
     0.0, -0.38268343236508978, -0.70710678118654752, -0.92387953251128674,
     -1.0, -0.92387953251128674, -0.70710678118654752, -0.38268343236508978};
 
-// v * exp(+2 pi i E / N) for compile-time E, N <= 16.
-template <typename R, int N, int E>
-__device__ __forceinline__ cplx<R> mul_root(cplx<R> v) {
+// Products are written with their rounding spelled out (which of the two terms
+// of a complex product's part is rounded before the fused multiply-add).  Left
+// to the compiler, the choice depends on the code around a butterfly, and the
+// variants of a pass (pruned, spreading fused in, persistent) would agree to
+// rounding only; FP64 plans would show it in nearly singular bins.
+//
+// a b: re = fma(a.x, b.x, -(a.y b.y)), im = fma(a.y, b.x, a.x b.y).
+__device__ __forceinline__ cplx<double> cmul_r(cplx<double> a, cplx<double> b) {
+  return cmk<double>(__builtin_fma(a.x, b.x, -(a.y * b.y)), __builtin_fma(a.y, b.x, a.x * b.y));
+}
+
+// v * exp(+2 pi i E / N) for compile-time E, N <= 16.  The y terms are rounded
+// first; X8: the x terms, for the eighth root E / N = 1/8.
+template <int N, int E, bool X8>
+__device__ __forceinline__ cplx<double> mul_root(cplx<double> v) {
   constexpr int e = E % N;
   if constexpr (e == 0) {
     return v;
   } else if constexpr (4 * e == N) {
-    return cmk<R>(-v.y, v.x);
+    return cmk<double>(-v.y, v.x);
   } else if constexpr (2 * e == N) {
-    return cmk<R>(-v.x, -v.y);
+    return cmk<double>(-v.x, -v.y);
   } else if constexpr (4 * e == 3 * N) {
-    return cmk<R>(v.y, -v.x);
+    return cmk<double>(v.y, -v.x);
   } else {
     constexpr int k = e * (16 / N);
-    const R c = (R)kC16[k];
-    const R s = (R)kS16[k];
-    return cmk<R>(v.x * c - v.y * s, v.x * s + v.y * c);
+    const double c = kC16[k];
+    const double s = kS16[k];
+    if constexpr (X8 && 8 * e == N) {
+      const double t = v.x * c;
+      return cmk<double>(__builtin_fma(-v.y, s, t), __builtin_fma(v.y, c, t));
+    }
+    return cmk<double>(__builtin_fma(v.x, c, -(v.y * s)), __builtin_fma(v.x, s, v.y * c));
   }
 }
+
+using C = cplx<double>;
 
 template <int N, int I>
 constexpr int bitrev() {
@@ -64,37 +82,41 @@ __device__ __forceinline__ void bitrev_perm(cplx<R>* v) {
   }
 }
 
-template <typename R, int N, int S, int K, int J>
-__device__ __forceinline__ void bfly_j(cplx<R>* v) {
+// RND: where the eighth roots round their x terms first (mul_root's X8).
+enum DftRound : int { RND_Y = 0, RND_X_LAST = 1, RND_X = 2 };
+
+template <int N, int S, int K, int J, int RND>
+__device__ __forceinline__ void bfly_j(C* v) {
   if constexpr (J < S) {
     constexpr int e = J * (N / (2 * S));
-    cplx<R> t = mul_root<R, N, e>(v[K + J + S]);
-    cplx<R> u = v[K + J];
+    constexpr bool x8 = RND == RND_X || (RND == RND_X_LAST && 2 * S == N);
+    C t = mul_root<N, e, x8>(v[K + J + S]);
+    C u = v[K + J];
     v[K + J] = cadd(u, t);
     v[K + J + S] = csub(u, t);
-    bfly_j<R, N, S, K, J + 1>(v);
+    bfly_j<N, S, K, J + 1, RND>(v);
   }
 }
-template <typename R, int N, int S, int K>
-__device__ __forceinline__ void bfly_k(cplx<R>* v) {
+template <int N, int S, int K, int RND>
+__device__ __forceinline__ void bfly_k(C* v) {
   if constexpr (K < N) {
-    bfly_j<R, N, S, K, 0>(v);
-    bfly_k<R, N, S, K + 2 * S>(v);
+    bfly_j<N, S, K, 0, RND>(v);
+    bfly_k<N, S, K + 2 * S, RND>(v);
   }
 }
-template <typename R, int N, int S>
-__device__ __forceinline__ void dit_stages(cplx<R>* v) {
+template <int N, int S, int RND>
+__device__ __forceinline__ void dit_stages(C* v) {
   if constexpr (S < N) {
-    bfly_k<R, N, S, 0>(v);
-    dit_stages<R, N, 2 * S>(v);
+    bfly_k<N, S, 0, RND>(v);
+    dit_stages<N, 2 * S, RND>(v);
   }
 }
 
 // In-register N-point DFT (N <= 16), natural order in and out, sign +i.
-template <typename R, int N>
-__device__ __forceinline__ void dft_reg(cplx<R>* v) {
-  bitrev_perm<R, N, 0>(v);
-  dit_stages<R, N, 1>(v);
+template <int N, int RND>
+__device__ __forceinline__ void dft_reg(C* v) {
+  bitrev_perm<double, N, 0>(v);
+  dit_stages<N, 1, RND>(v);
 }
 
 // A tile holds 2^12 complex elements, or 2^13 with FP32 grids (the same LDS
@@ -106,30 +128,32 @@ template <typename S>
 constexpr int tile_log_max() {
   return sizeof(S) == 4 ? 13 : 12;
 }
-using C = cplx<double>;
 
-// Grid data each pass touches once.  Runs of at least 128 bytes (NT) are
-// loaded and stored non-temporally (streaming); shorter runs measured slower
-// that way and use ordinary accesses.
+// Grid data each pass touches once: element `off` bytes past a base that is
+// the same for the whole workgroup, so that a lane's address is one 32-bit
+// register (a pair's grid is at most 2^30 bytes).  Runs of at least 128 bytes
+// (NT) are loaded and stored non-temporally (streaming); shorter runs measured
+// slower that way and use ordinary accesses.
+template <typename S, int W>
+using vecS = S __attribute__((ext_vector_type(W)));
 template <bool NT, typename S>
-__device__ __forceinline__ cplx<S> ntl(const cplx<S>* p) {
-  if constexpr (NT) {
-    cplx<S> r;
-    r.x = __builtin_nontemporal_load(&p->x);
-    r.y = __builtin_nontemporal_load(&p->y);
-    return r;
-  } else {
-    return *p;
-  }
+__device__ __forceinline__ cplx<S> ntl(const char* base, uint32_t off) {
+  const vecS<S, 2>* p = (const vecS<S, 2>*)(base + off);
+  vecS<S, 2> r;
+  if constexpr (NT)
+    r = __builtin_nontemporal_load(p);
+  else
+    r = *p;
+  return cmk<S>(r.x, r.y);
 }
 template <bool NT, typename S>
-__device__ __forceinline__ void nts(cplx<S>* p, cplx<S> v) {
-  if constexpr (NT) {
-    __builtin_nontemporal_store(v.x, &p->x);
-    __builtin_nontemporal_store(v.y, &p->y);
-  } else {
-    *p = v;
-  }
+__device__ __forceinline__ void nts(char* base, uint32_t off, cplx<S> v) {
+  vecS<S, 2>* p = (vecS<S, 2>*)(base + off);
+  vecS<S, 2> r = {v.x, v.y};
+  if constexpr (NT)
+    __builtin_nontemporal_store(r, p);
+  else
+    *p = r;
 }
 template <typename S>
 __device__ __forceinline__ C widen(cplx<S> v) {
@@ -164,11 +188,37 @@ struct Stage {
   }
 };
 
-// Butterflies of one stage on the registers (FP64): stage twiddles from the
-// omega_{2^13} table, then the in-register RAD-point DFT.
-template <int LOGN, int LOGT, int LOGNS>
-__device__ __forceinline__ void stage_compute(C* v, const C* __restrict__ tw, int tid) {
+// Stage twiddles of a tile kept in LDS (FP32 grids, tiles of more than one
+// column): the second stage's omega_{16 RAD}^{j i}, row i - 1, column j < 16,
+// and for tiles of 2^9 rows the third stage's omega_512^j, j < 256.  Read from
+// the global table every thread would gather 15 to 23 entries of 16 bytes per
+// tile through the L1 beside the tile's own 16 loads.  FP64 tiles fill the LDS
+// with data and single-column tiles have longer tables: both read the global
+// table.
+template <typename S, int LOGN, int LOGT>
+struct StageTw {
+  static constexpr bool kLds = sizeof(S) == 4 && LOGT > 0 && LOGN > 4;
+  static constexpr int LR2 = LOGN - 4 >= 4 ? 4 : (LOGN > 4 ? LOGN - 4 : 0);
+  static constexpr int N2 = kLds ? ((1 << LR2) - 1) * 16 : 0;
+  static constexpr int N3 = kLds && LOGN > 8 ? 256 : 0;
+  static_assert(!kLds || LOGN <= 9, "third stage of radix 2 at most");
+  static constexpr int SIZE = N2 + N3 > 0 ? N2 + N3 : 1;
+  __device__ static void fill(C* t, const C* __restrict__ tw, int tid, int nt) {
+    if constexpr (kLds) {
+      for (int e = tid; e < N2; e += nt)
+        t[e] = tw[((e & 15) * ((e >> 4) + 1)) << (kStageLog - 4 - LR2)];
+      for (int e = tid; e < N3; e += nt) t[N2 + e] = tw[e << (kStageLog - 9)];
+    }
+  }
+};
+
+// Butterflies of one stage on the registers (FP64): stage twiddles (LDS, or
+// the omega_{2^13} table), then the in-register RAD-point DFT.
+template <typename S, int LOGN, int LOGT, int LOGNS>
+__device__ __forceinline__ void stage_compute(C* v, const C* __restrict__ tw, const C* tl,
+                                              int tid) {
   using St = Stage<LOGN, LOGT, LOGNS>;
+  using Tw = StageTw<S, LOGN, LOGT>;
   constexpr int TWS = kStageLog - LOGNS - St::LOGRAD;
   static_assert(TWS >= 0, "stage twiddle table too small");
 #pragma unroll
@@ -177,24 +227,50 @@ __device__ __forceinline__ void stage_compute(C* v, const C* __restrict__ tw, in
     if constexpr (St::NS > 1) {
       const int j = St::bfly(tid, it) & (St::NS - 1);
 #pragma unroll
-      for (int i = 1; i < St::RAD; ++i) u[i] = cmul(u[i], tw[(j * i) << TWS]);
+      for (int i = 1; i < St::RAD; ++i) {
+        if constexpr (Tw::kLds)
+          u[i] = cmul_r(u[i], tl[LOGNS == 4 ? (i - 1) * 16 + j : Tw::N2 + j]);
+        else
+          u[i] = cmul_r(u[i], tw[(j * i) << TWS]);
+      }
     }
-    dft_reg<double, St::RAD>(u);
+    // First stage of 2^6 and 2^7 rows, of other tiles, later stages.
+    constexpr int RND = LOGNS > 0 ? RND_X : (LOGN == 6 || LOGN == 7 ? RND_Y : RND_X_LAST);
+    dft_reg<St::RAD, RND>(u);
   }
 }
 
+// Row pitch of a tile in LDS and the place of column c in row r.  A row of 16
+// or more FP32 elements is 128 bytes or more, so sixteen lanes of an exchange
+// between stages cover all banks without padding; where columns are read
+// (tile_col: the first pass's transposition) the columns of a row are permuted
+// by its low bits instead.  Shorter rows, and FP64 rows, have a padding column.
+template <typename S, int LOGT>
+constexpr bool tile_swizzled() {
+  return sizeof(S) == 4 && LOGT >= 4;
+}
+template <typename S, int LOGT>
+constexpr int tile_pitch() {
+  return LOGT == 0 || tile_swizzled<S, LOGT>() ? (1 << LOGT) : (1 << LOGT) + 1;
+}
+template <typename S, int LOGT>
+__device__ __forceinline__ int tile_col(int r, int c) {
+  return r * tile_pitch<S, LOGT>() + (tile_swizzled<S, LOGT>() ? c ^ (r & 15) : c);
+}
+
 // Run the stages from LOGNS on; between stages the registers go through the
-// LDS tile (type S) in Stockham order.  On return v holds the last stage's
-// outputs: element i of slot it is row out_row(b, i) of column col(tid, it).
-template <typename S, int LOGN, int LOGT, int LOGNS>
+// LDS tile (type S, row pitch PT) in Stockham order.  On return v holds the
+// last stage's outputs: element i of slot it is row out_row(b, i) of column
+// col(tid, it).  FENCE: other threads may still be reading the tile when the
+// first exchange writes it.
+template <typename S, int LOGN, int LOGT, int LOGNS, int PT, bool FENCE>
 __device__ __forceinline__ void run_stages(C* v, cplx<S>* sm, const C* __restrict__ tw,
-                                           int tid) {
+                                           const C* tl, int tid) {
   using St = Stage<LOGN, LOGT, LOGNS>;
-  constexpr int PT = (St::T == 1) ? 1 : St::T + 1;
-  stage_compute<LOGN, LOGT, LOGNS>(v, tw, tid);
+  stage_compute<S, LOGN, LOGT, LOGNS>(v, tw, tl, tid);
   if constexpr (!St::LAST) {
     using Nx = Stage<LOGN, LOGT, LOGNS + St::LOGRAD>;
-    __syncthreads();  // previous readers of sm are done
+    if constexpr (FENCE || LOGNS > 0) __syncthreads();  // previous readers of sm are done
 #pragma unroll
     for (int it = 0; it < St::PER; ++it) {
       const int c = St::col(tid, it), b = St::bfly(tid, it);
@@ -210,7 +286,7 @@ __device__ __forceinline__ void run_stages(C* v, cplx<S>* sm, const C* __restric
       for (int i = 0; i < Nx::RAD; ++i)
         v[it * Nx::RAD + i] = widen(sm[Nx::in_row(b, i) * PT + c]);
     }
-    run_stages<S, LOGN, LOGT, LOGNS + St::LOGRAD>(v, sm, tw, tid);
+    run_stages<S, LOGN, LOGT, LOGNS + St::LOGRAD, PT, FENCE>(v, sm, tw, tl, tid);
   }
 }
 
@@ -248,7 +324,6 @@ __device__ __forceinline__ void spread_into_tile(const FftPassArgs& a, const Mom
                                                  int64_t r_lim, cplx<S>* sm, int tid) {
   constexpr int N = 1 << LOGN;
   constexpr int T = 1 << LOGT;
-  constexpr int PT = (T == 1) ? 1 : T + 1;
   constexpr int NTH = (N * T) / kEPT;
   constexpr int CPR = T >= kEPT ? kEPT : T;  // cells per owned row segment
   constexpr int RPT = kEPT / CPR;            // row segments per thread
@@ -337,31 +412,52 @@ __device__ __forceinline__ void spread_into_tile(const FftPassArgs& a, const Mom
     const int c0 = (TPR > 1) ? (tid % TPR) * kEPT : 0;
 #pragma unroll
     for (int u = 0; u < CPR; ++u)
-      sm[row * PT + c0 + u] = cmk<S>((S)ar[j][u], (S)ai[j][u]);
+      sm[tile_col<S, LOGT>(row, c0 + u)] = cmk<S>((S)ar[j][u], (S)ai[j][u]);
   }
   __syncthreads();
 }
+
+// The variants of a pass: the first (TILE_FIRST2: of two passes), middle and
+// single passes, the last forward pass of an ordinary plan (TILE_LAST: the half
+// of the outputs that no bin needs is known at compile time) and any other last
+// pass (TILE_LAST_ANY: band plans and the adjoint).
+enum TileKind : int {
+  TILE_FIRST = 0,
+  TILE_MID = 1,
+  TILE_LAST = 2,
+  TILE_LAST_ANY = 3,
+  TILE_SINGLE = 4,
+  TILE_FIRST2 = 5
+};
+constexpr bool kind_first(int kind) { return kind == TILE_FIRST || kind == TILE_FIRST2; }
 
 // One pass.  Twiddles between passes, for output row k of tile column cc:
 //   PASS_FIRST, np >= 3: w_M^{jd k}        (jd fixed for the tile)   = r[k]
 //   PASS_FIRST, np == 2: w_L^{(g0+cc) k}   = r[k] * small[cc k]
 //   PASS_MID:            w_M^{jd (K0+cc+Tail k)}                     = c[cc] r[k]
-// with r, c built per workgroup in FP64 and small[e] = w_L^e, e < N T.
-// LDS of one tile: the data tile, the row and column twiddles and, in the
-// first pass, the output offset of each tile column.
-// FP64 tiles keep the row twiddles in the padding column of the data tile
-// (one 16-byte slot per row that no data access touches), which brings the
-// 2^9 x 8 tile from 82 to 74 KB: two workgroups per CU instead of one.
-template <typename S, int LOGN, int LOGT>
+// with r, c built per workgroup in FP64 from exactly reduced exponents and
+// small[e] = w_L^e, e < N T, laid out in thread order (tw_tile).
+//
+// LDS of one tile: the data tile, the stage twiddles (FP32), the row and
+// column twiddles and, in the first pass, the output offset of each tile
+// column.  FP64 tiles keep the row twiddles in the padding column of the data
+// tile (one 16-byte slot per row that no data access touches), which brings
+// the 2^9 x 8 tile from 82 to 74 KB: two workgroups per CU instead of one.
+// The FP32 tile of 2^9 x 16 takes the 80 KB that two workgroups per CU allow.
+template <typename S, int LOGN, int LOGT, int KIND>
 struct FftSmem {
   static constexpr int N = 1 << LOGN;
   static constexpr int T = 1 << LOGT;
-  static constexpr int PT = (T == 1) ? 1 : T + 1;
+  static constexpr int PT = tile_pitch<S, LOGT>();
   static constexpr bool kTrInPad = sizeof(cplx<S>) == sizeof(C) && T > 1;
+  static constexpr bool kTw = kind_first(KIND) || KIND == TILE_MID;
   __align__(16) cplx<S> sm[N * PT];
-  C tr[(T == 1 || kTrInPad) ? 1 : N];  // the single-pass tile has no twiddles
-  C tc[T];
-  int64_t s_rev[T];
+  C st[StageTw<S, LOGN, LOGT>::SIZE];
+  C tr[kTw && !kTrInPad ? N : 1];
+  // middle pass: column twiddles; first pass: output byte offset of each column
+  C aux[KIND == TILE_MID ? T : (kind_first(KIND) ? (T + 3) / 4 : 1)];
+  __device__ __forceinline__ C* tc() { return aux; }
+  __device__ __forceinline__ uint32_t* s_rev() { return reinterpret_cast<uint32_t*>(aux); }
   __device__ __forceinline__ C& row_tw(int k) {
     if constexpr (kTrInPad)
       return *reinterpret_cast<C*>(&sm[k * PT + T]);
@@ -374,143 +470,160 @@ struct FftSmem {
 // cw, whose grid is at in + grid_off (input) and out + grid_off (output) and
 // whose pruned spectra (last forward pass) start at zpair.  Every thread of
 // the workgroup calls it (it synchronises the workgroup).
-template <typename S, int LOGN, int LOGT, bool FUSED>
+//
+// What bounds it: HBM, once the work per element is small enough to hide.  The
+// rows a thread loads and stores are b0 + (N/16) j of one column, so every
+// address is one per-thread 32-bit offset past a uniform base.
+template <typename S, int LOGN, int LOGT, bool FUSED, int KIND>
 __device__ __forceinline__ void fft_pass_tile(const FftPassArgs& a, const cplx<S>* in,
                                               cplx<S>* out, const Moments* __restrict__ mom,
                                               const Geom& g, const C* __restrict__ tw_stage,
-                                              const C* __restrict__ tw_small, int bx, int p,
-                                              int cw, int64_t grid_off, cplx<S>* zpair,
-                                              FftSmem<S, LOGN, LOGT>& sh, int tid) {
+                                              int bx, int p, int cw, int64_t grid_off, cplx<S>* zpair,
+                                              FftSmem<S, LOGN, LOGT, KIND>& sh,
+                                              int tid) {
   constexpr int N = 1 << LOGN;
   constexpr int T = 1 << LOGT;
-  constexpr int PT = (T == 1) ? 1 : T + 1;
+  constexpr bool FIRST = kind_first(KIND);
+  constexpr int PT = tile_pitch<S, LOGT>();
   constexpr int kNT = (N * T) / kEPT;  // threads of this tile
+  constexpr int R16 = N / kEPT;        // row step of a thread's elements
+  constexpr uint32_t ES = sizeof(cplx<S>);
   static_assert(N * T == 4096 || (N * T == 8192 && sizeof(S) == 4), "tile size");
+  static_assert(!FUSED || FIRST, "the spreading is fused into the first pass");
   constexpr bool NT = T * sizeof(cplx<S>) >= 128;
   using S0 = Stage<LOGN, LOGT, 0>;
   using SL = Stage<LOGN, LOGT, last_logns(LOGN)>;
+  using Tw = StageTw<S, LOGN, LOGT>;
   cplx<S>* sm = sh.sm;
-  C* tc = sh.tc;
-  int64_t* s_rev = sh.s_rev;
 
-  const Moments mo = mom[a.curve0 + cw];
+  const Moments& mo = mom[a.curve0 + cw];
   if (mo.flags & kCurveFatal) return;
 
-  const int64_t L = g.L;
   const int logL = a.logL;
-  const cplx<S>* src = in + grid_off;
-  const int64_t g0 = (int64_t)bx * T;  // first column of this tile
+  const uint32_t L = 1u << logL;
+  const char* src = (const char*)(in + grid_off);
+  char* dst = (char*)(out + grid_off);
+  const uint32_t g0 = (uint32_t)bx << LOGT;  // first column of this tile
 
   int low_bits = 0;  // sum of log2 N over digits below q
-  for (int d = 1; d < a.q; ++d) low_bits += a.logn[d];
+  if constexpr (KIND == TILE_MID)
+    for (int d = 1; d < a.q; ++d) low_bits += a.logn[d];
+  // Column c = g0 + cc of the tile: its rows are 2^logS elements apart, from
+  // element `first` + cc on (PASS_MID: column (pre, K0 + cc) of the digit-
+  // reversed layout, the others' rows span the whole grid).
+  const int logS = logL - low_bits - LOGN;
+  uint32_t pre = 0, K0 = g0, first = g0;
+  if constexpr (KIND == TILE_MID) {
+    pre = g0 >> logS;
+    K0 = g0 - (pre << logS);
+    first = (pre << (LOGN + logS)) + K0;
+  }
+  // Thread: column cc, rows b0 + R16 j.
+  const uint32_t cc0 = (uint32_t)tid & (T - 1), b0 = (uint32_t)tid >> LOGT;
+  const uint32_t voff = ((b0 << logS) + cc0) * ES;
+  const uint64_t rstep = (uint64_t)(R16 * ES) << logS;  // bytes between its rows
+  const char* rb = src + (uint64_t)first * ES;
+
+  Tw::fill(sh.st, tw_stage, tid, kNT);
 
   C v[kEPT];
-  // Stage-0 inputs straight from HBM: element i of slot it is row
-  // in_row(b, i) of column col(tid, it).
-  if (a.kind == PASS_FIRST || a.kind == PASS_SINGLE) {
-    const int64_t Sd = L >> LOGN;  // column c = g0 + cc, row r at c + Sd r
-    int64_t r_skip_lo, r_skip_hi;  // rows in [r_skip_lo, r_skip_hi) are zero
+  // Stage-0 inputs straight from HBM: element i is row b0 + R16 i.
+  static_assert(S0::PER == 1, "one radix-16 butterfly per thread in the first stage");
+  if constexpr (FIRST || KIND == TILE_SINGLE) {
+    uint32_t z_lo, z_hi;  // rows in [z_lo, z_hi) are zero
     if (a.mode == MODE_FWD) {
       const int64_t E = pair_extent(mo, g, p);
-      r_skip_lo = (E + Sd - 1) / Sd;
-      r_skip_hi = N;
+      z_lo = (uint32_t)((E + ((int64_t)1 << logS) - 1) >> logS);
+      z_hi = N;
     } else {
-      r_skip_lo = g.n_freq / Sd;
-      r_skip_hi = (L - g.n_freq) / Sd;
+      z_lo = (uint32_t)(g.n_freq >> logS);
+      z_hi = (uint32_t)((g.L - g.n_freq) >> logS);
     }
     if constexpr (FUSED) {
       // Forward first pass only (the launcher guarantees it).
       if (g.w == 1)
-        spread_into_tile<S, LOGN, LOGT, true>(a, mo, g, p, cw, g0, r_skip_lo, sm, tid);
+        spread_into_tile<S, LOGN, LOGT, true>(a, mo, g, p, cw, g0, z_lo, sm, tid);
       else
-        spread_into_tile<S, LOGN, LOGT, false>(a, mo, g, p, cw, g0, r_skip_lo, sm, tid);
+        spread_into_tile<S, LOGN, LOGT, false>(a, mo, g, p, cw, g0, z_lo, sm, tid);
 #pragma unroll
-      for (int it = 0; it < S0::PER; ++it) {
-        const int cc = S0::col(tid, it), b = S0::bfly(tid, it);
-#pragma unroll
-        for (int i = 0; i < S0::RAD; ++i)
-          v[it * S0::RAD + i] = widen(sm[S0::in_row(b, i) * PT + cc]);
-      }
+      for (int i = 0; i < kEPT; ++i) v[i] = widen(sm[tile_col<S, LOGT>(b0 + i * R16, cc0)]);
     } else {
 #pragma unroll
-      for (int it = 0; it < S0::PER; ++it) {
-        const int cc = S0::col(tid, it), b = S0::bfly(tid, it);
-#pragma unroll
-        for (int i = 0; i < S0::RAD; ++i) {
-          const int r = S0::in_row(b, i);
-          C val = cmk<double>(0.0, 0.0);
-          if (r < r_skip_lo || r >= r_skip_hi) val = widen(ntl<NT>(&src[g0 + cc + Sd * r]));
-          v[it * S0::RAD + i] = val;
-        }
-      }
-    }
-    if (a.kind == PASS_FIRST) {
-      const int np = a.np;
-      const int logM = a.logn[np - 1] + LOGN;
-      if (np >= 3) {
-        int bits_below = 0;
-        for (int d = 1; d < np - 1; ++d) bits_below += a.logn[d];
-        const int64_t jd = g0 >> bits_below;
-        const int64_t Mmask = ((int64_t)1 << logM) - 1;
-        for (int k = tid; k < N; k += kNT) sh.row_tw(k) = root((jd * k) & Mmask, logM);
-      } else {
-        for (int k = tid; k < N; k += kNT) sh.row_tw(k) = root((g0 * k) & (L - 1), logL);
+      for (int i = 0; i < kEPT; ++i) {
+        const uint32_t r = b0 + i * R16;
+        C val = cmk<double>(0.0, 0.0);
+        if (r < z_lo || r >= z_hi) val = widen(ntl<NT, S>(rb + i * rstep, voff));
+        v[i] = val;
       }
     }
   } else {
-    // PASS_MID: column (pre, K0 + cc), row r at pre N Tail + r Tail + K0 + cc.
-    // PASS_LAST: pre = 0, Tail = L / N.
-    const int64_t Tail = L >> (low_bits + LOGN);
-    const int64_t pre = g0 / Tail;
-    const int64_t K0 = g0 - pre * Tail;
-    const cplx<S>* base = src + pre * ((int64_t)N * Tail) + K0;
 #pragma unroll
-    for (int it = 0; it < S0::PER; ++it) {
-      const int cc = S0::col(tid, it), b = S0::bfly(tid, it);
-#pragma unroll
-      for (int i = 0; i < S0::RAD; ++i)
-        v[it * S0::RAD + i] = widen(ntl<NT>(&base[(int64_t)S0::in_row(b, i) * Tail + cc]));
-    }
-    if (a.kind == PASS_MID) {
-      const int64_t jd = pre & (((int64_t)1 << a.logn[a.q - 1]) - 1);
-      const int logTail = logL - low_bits - LOGN;
-      const int logM = a.logn[a.q - 1] + LOGN + logTail;
-      const int64_t Mmask = ((int64_t)1 << logM) - 1;
-      for (int k = tid; k < N; k += kNT) sh.row_tw(k) = root((jd * Tail * k) & Mmask, logM);
-      for (int cc = tid; cc < T; cc += kNT) tc[cc] = root((jd * (K0 + cc)) & Mmask, logM);
-    }
+    for (int i = 0; i < kEPT; ++i) v[i] = widen(ntl<NT, S>(rb + i * rstep, voff));
   }
-  // tr/tc become visible at the first barrier inside run_stages, or below.
-  run_stages<S, LOGN, LOGT, 0>(v, sm, tw_stage, tid);
+
+  if constexpr (KIND == TILE_FIRST) {
+    const int np = a.np;
+    const int logM = a.logn[np - 1] + LOGN;
+    int bits_below = 0;
+    for (int d = 1; d < np - 1; ++d) bits_below += a.logn[d];
+    const int64_t jd = (int64_t)(g0 >> bits_below);
+    const int64_t Mmask = ((int64_t)1 << logM) - 1;
+    for (int k = tid; k < N; k += kNT) sh.row_tw(k) = root((jd * k) & Mmask, logM);
+  } else if constexpr (KIND == TILE_FIRST2) {
+    for (int k = tid; k < N; k += kNT)
+      sh.row_tw(k) = root(((int64_t)g0 * k) & ((int64_t)L - 1), logL);
+  } else if constexpr (KIND == TILE_MID) {
+    const int lg = a.logn[a.q - 1];
+    const int64_t jd = pre & ((1u << lg) - 1u);
+    const int logM = lg + LOGN + logS;
+    const int64_t Mmask = ((int64_t)1 << logM) - 1;
+    for (int k = tid; k < N; k += kNT) sh.row_tw(k) = root(((jd << logS) * k) & Mmask, logM);
+    for (int cc = tid; cc < T; cc += kNT) sh.tc()[cc] = root((jd * (K0 + cc)) & Mmask, logM);
+  }
+
+  // The LDS twiddles become visible at the barriers inside run_stages, or below.
+  run_stages<S, LOGN, LOGT, 0, PT, FUSED>(v, sm, tw_stage, sh.st, tid);
   if constexpr (last_logns(LOGN) == 0) __syncthreads();  // single-stage tile
 
-  cplx<S>* dst = out + grid_off;
-  if (a.kind == PASS_FIRST) {
-    // Twiddle in registers, then transpose through LDS so that each column's
-    // N outputs leave as one contiguous run at row rev(c) of the output.
+  // Output row b0 + R16 j is element j / PER of butterfly slot j % PER.
+  auto at = [&](int j) -> C& { return v[(j % SL::PER) * SL::RAD + j / SL::PER]; };
+  if constexpr (KIND == TILE_FIRST) {
+#pragma unroll
+    for (int j = 0; j < kEPT; ++j) at(j) = cmul_r(at(j), sh.row_tw(b0 + R16 * j));
+  } else if constexpr (KIND == TILE_FIRST2) {
+    const C* tt = (const C*)a.tw_tile + tid;
+    constexpr int kGroup = SL::PER > 1 ? 2 : 4;
+#pragma unroll
+    for (int j = 0; j < kEPT; ++j) {
+      at(j) = cmul_r(at(j), cmul_r(sh.row_tw(b0 + R16 * j), tt[j * kNT]));
+      // All sixteen loads in flight at once would take the registers of two
+      // more workgroups (or spill); a few at a time hide behind the products.
+      if (j % kGroup == kGroup - 1) __builtin_amdgcn_sched_barrier(0);
+    }
+  } else if constexpr (KIND == TILE_MID) {
+    const C fc = sh.tc()[cc0];
+#pragma unroll
+    for (int j = 0; j < kEPT; ++j)
+      at(j) = cmul_r(at(j), cmul_r(fc, sh.row_tw(b0 + R16 * j)));
+  }
+
+  if constexpr (FIRST) {
+    // Transpose through LDS so that each column's N outputs leave as one
+    // contiguous run at row rev(c) of the output.
     const int np = a.np;
     __syncthreads();
 #pragma unroll
-    for (int it = 0; it < SL::PER; ++it) {
-      const int cc = SL::col(tid, it), b = SL::bfly(tid, it);
-#pragma unroll
-      for (int i = 0; i < SL::RAD; ++i) {
-        const int k = SL::out_row(b, i);
-        C tw = sh.row_tw(k);
-        if (np == 2) tw = cmul(tw, tw_small[cc * k]);
-        sm[k * PT + cc] = narrow<S>(cmul(v[it * SL::RAD + i], tw));
-      }
-    }
+    for (int j = 0; j < kEPT; ++j) sm[tile_col<S, LOGT>(b0 + R16 * j, cc0)] = narrow<S>(at(j));
     // Mixed-radix reversal of each of the tile's T columns, once per tile:
     // rev = ((j_1 N_2 + j_2) N_3 + j_3) ... + j_{np-1} for column c = g0 + cc.
     for (int cc = tid; cc < T; cc += kNT) {
-      int64_t rev = 0, rest = g0 + cc;
+      uint32_t rev = 0, rest = g0 + cc;
       for (int d = 1; d < np; ++d) {
-        const int64_t dig = rest & (((int64_t)1 << a.logn[d]) - 1);
+        const uint32_t dig = rest & ((1u << a.logn[d]) - 1u);
         rest >>= a.logn[d];
         rev = (rev << a.logn[d]) | dig;
       }
-      s_rev[cc] = rev * N;
+      sh.s_rev()[cc] = rev * (N * ES);
     }
     __syncthreads();
 #pragma unroll 4
@@ -518,53 +631,52 @@ __device__ __forceinline__ void fft_pass_tile(const FftPassArgs& a, const cplx<S
       const int e = tid + it * kNT;
       const int k = e & (N - 1);
       const int cc = e >> LOGN;
-      nts<NT>(&dst[s_rev[cc] + k], sm[k * PT + cc]);
+      nts<NT, S>(dst, sh.s_rev()[cc] + k * ES, sm[tile_col<S, LOGT>(k, cc)]);
     }
-  } else if (a.kind == PASS_MID) {
-    const int64_t Tail = L >> (low_bits + LOGN);
-    const int64_t pre = g0 / Tail;
-    const int64_t K0 = g0 - pre * Tail;
-    cplx<S>* base = dst + pre * ((int64_t)N * Tail) + K0;
+  } else if constexpr (KIND == TILE_MID) {
+    char* wb = dst + (uint64_t)first * ES;
 #pragma unroll
-    for (int it = 0; it < SL::PER; ++it) {
-      const int cc = SL::col(tid, it), b = SL::bfly(tid, it);
-      const C fc = tc[cc];
+    for (int j = 0; j < kEPT; ++j) nts<NT, S>(wb + j * rstep, voff, narrow<S>(at(j)));
+  } else if constexpr (KIND == TILE_LAST) {
+    // X = g0 + cc + Tail k: bins X < n_freq = L / 4 (rows j < 4) to the direct
+    // half and L - X < n_freq (j >= 12, but for row 12's X = L - n_freq) to the
+    // mirror half, X = 0 to both.
+    char* z0 = (char*)zpair;
+    char* z1 = (char*)(zpair + (L >> 2));
 #pragma unroll
-      for (int i = 0; i < SL::RAD; ++i) {
-        const int k = SL::out_row(b, i);
-        nts<NT>(&base[(int64_t)k * Tail + cc], narrow<S>(cmul(v[it * SL::RAD + i], cmul(fc, sh.row_tw(k)))));
-      }
+    for (int j = 0; j < 4; ++j) {
+      const cplx<S> val = narrow<S>(at(j));
+      nts<false, S>(z0 + (uint64_t)g0 * ES + j * rstep, voff, val);
+      if (j == 0 && bx == 0 && tid == 0) nts<false, S>(z1, 0, val);
+    }
+    // Mirror bin L - X, counted from the tile's row 16 (j + 1) back.
+    const uint32_t moff = (uint32_t)rstep - voff;
+#pragma unroll
+    for (int j = 12; j < kEPT; ++j) {
+      char* zb = z1 + (int64_t)(15 - j) * (int64_t)rstep - (int64_t)g0 * ES;
+      if (j > 12 || bx != 0 || tid != 0) nts<false, S>(zb, moff, narrow<S>(at(j)));
     }
   } else {
     // PASS_LAST / PASS_SINGLE: X index = K + Tail * k, natural order.
-    const int64_t Tail = L >> LOGN;
-    const int64_t nf = g.n_freq;
     if (a.mode == MODE_FWD) {
+      const uint32_t nf = (uint32_t)g.n_freq;
       cplx<S>* z0 = zpair;
       cplx<S>* z1 = z0 + nf;
 #pragma unroll
-      for (int it = 0; it < SL::PER; ++it) {
-        const int cc = SL::col(tid, it), b = SL::bfly(tid, it);
-#pragma unroll
-        for (int i = 0; i < SL::RAD; ++i) {
-          const int64_t X = g0 + cc + Tail * SL::out_row(b, i);
-          const cplx<S> val = narrow<S>(v[it * SL::RAD + i]);
-          if (X < nf) z0[X] = val;
-          const int64_t Xm = (L - X) & (L - 1);
-          if (Xm < nf) z1[Xm] = val;
-        }
+      for (int j = 0; j < kEPT; ++j) {
+        const uint32_t X = g0 + cc0 + ((b0 + R16 * j) << logS);
+        const cplx<S> val = narrow<S>(at(j));
+        if (X < nf) z0[X] = val;
+        const uint32_t Xm = (L - X) & (L - 1);
+        if (Xm < nf) z1[Xm] = val;
       }
     } else {
-      const int64_t E = pair_extent(mo, g, p);
+      const uint32_t E = (uint32_t)pair_extent(mo, g, p);
       cplx<S>* go = (cplx<S>*)a.grid_out + grid_off;
 #pragma unroll
-      for (int it = 0; it < SL::PER; ++it) {
-        const int cc = SL::col(tid, it), b = SL::bfly(tid, it);
-#pragma unroll
-        for (int i = 0; i < SL::RAD; ++i) {
-          const int64_t X = g0 + cc + Tail * SL::out_row(b, i);
-          if (X < E) go[X] = narrow<S>(v[it * SL::RAD + i]);
-        }
+      for (int j = 0; j < kEPT; ++j) {
+        const uint32_t X = g0 + cc0 + ((b0 + R16 * j) << logS);
+        if (X < E) go[X] = narrow<S>(at(j));
       }
     }
   }
@@ -582,18 +694,32 @@ constexpr int fft_pass_waves() {
   return (sizeof(S) == 4 && !FUSED) ? 4 : 1;
 }
 
+// Thread-order twiddles of the two-pass first pass: out[j NT + tid] =
+// small[cc k] for thread tid's row k = b0 + (N / 16) j of column cc, for a tile
+// of 2^logn rows and 2^logt columns.  The tile's threads read it coalesced;
+// gathered from small[] itself (16 entries of 16 bytes per thread, up to 64
+// cache lines per load) it took most of that pass.
+__global__ void k_tile_tw(const C* __restrict__ small, int logn, int logt, C* __restrict__ out) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= 1 << (logn + logt)) return;
+  const int nt = 1 << (logn + logt - 4);
+  const int tid = e & (nt - 1), j = e / nt;
+  const int cc = tid & ((1 << logt) - 1), k = (tid >> logt) + ((1 << logn) >> 4) * j;
+  out[e] = small[cc * k];
+}
+
 // The pass over a wave of curves: grid (column tiles, pairs, curves).
-template <typename S, int LOGN, int LOGT, bool FUSED>
+template <typename S, int LOGN, int LOGT, bool FUSED, int KIND>
 __global__ __launch_bounds__(((1 << LOGN) << LOGT) / kEPT, (fft_pass_waves<S, FUSED>())) void k_fft_pass(
     FftPassArgs a, const cplx<S>* in, cplx<S>* out, const Moments* __restrict__ mom, Geom g,
-    const C* __restrict__ tw_stage, const C* __restrict__ tw_small) {
-  __shared__ FftSmem<S, LOGN, LOGT> sh;
+    const C* __restrict__ tw_stage) {
+  __shared__ FftSmem<S, LOGN, LOGT, KIND> sh;
   const int p = blockIdx.y;
   const int cw = blockIdx.z;
   const int64_t grid_off = ((int64_t)cw * g.P + p) * g.L;
   cplx<S>* zpair = a.zc ? (cplx<S>*)a.zc + ((int64_t)cw * g.P + p) * 2 * g.n_freq : nullptr;
-  fft_pass_tile<S, LOGN, LOGT, FUSED>(a, in, out, mom, g, tw_stage, tw_small, blockIdx.x, p, cw,
-                                      grid_off, zpair, sh, threadIdx.x);
+  fft_pass_tile<S, LOGN, LOGT, FUSED, KIND>(a, in, out, mom, g, tw_stage, blockIdx.x, p, cw,
+                                            grid_off, zpair, sh, threadIdx.x);
 }
 
 }  // namespace

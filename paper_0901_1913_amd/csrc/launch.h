@@ -22,6 +22,7 @@ struct FftPassArgs {
   const int32_t* tb;           // fused: tile table of tiles of 2^tb_log cells
   int tb_log;                  //   (2^tb_log >= w + 3), ntb entries per harmonic
   int ntb;
+  const void* tw_tile;         // first pass of two: thread-order twiddles of its tile
 };
 
 // Moments, validity flags and chi2_0 of every curve: bpc workgroups per
@@ -49,10 +50,13 @@ hipError_t launch_tile_bounds(const double* t, const Moments* mom, const Geom& g
 
 // log2 of the elements of the largest FFT tile (rows x columns held in LDS).
 int fft_tile_log(bool fp64);
-// tws: omega_{2^13}^e (FP64), twsm: omega_L^e for e < 2^fft_tile_log(fp64) (FP64).
+// tws: omega_{2^13}^e (FP64).
 hipError_t launch_fft_pass(bool fp64, const FftPassArgs& a, int logn, int logt, const void* in,
                            void* out, const Moments* mom, const Geom& g, const void* tws,
-                           const void* twsm, int n_curves, int64_t ncols, hipStream_t st);
+                           int n_curves, int64_t ncols, hipStream_t st);
+// Thread-order twiddles of a two-pass first pass with tiles of 2^logn rows x
+// 2^logt columns, from small[e] = omega_L^e (FP64), e < 2^(logn + logt).
+hipError_t launch_tile_tw(const void* small, int logn, int logt, void* out, hipStream_t st);
 
 // Persistent batched search (MIXED plans, H <= 8, FFT splits of 4096-element
 // tiles with 2^5..2^9 rows per pass, spreading tiles of 2^10 or 2^11 cells):
@@ -71,7 +75,6 @@ struct PersistArgs {
   // pass so that the kernel indexes the split from its argument block.
   FftPassArgs fa[kMaxPasses + 1];
   const cplx<double>* tws;
-  const cplx<double>* twsm;
   const cplx<double>* D;
   int curve_base;
   int n_curves;

@@ -31,11 +31,12 @@ constexpr size_t cmax(T a, T b) {
 }
 
 // LDS of the largest stage: FFT tiles of 4096 FP32 elements (N = 2^5..2^9
-// rows) and spreading tiles of 1024 or 2048 cells.
+// rows; the middle pass's hold the most) and spreading tiles of 1024 or 2048
+// cells.
 constexpr size_t kSmemBytes =
-    cmax(cmax(cmax(sizeof(FftSmem<float, 5, 7>), sizeof(FftSmem<float, 6, 6>)),
-              cmax(sizeof(FftSmem<float, 7, 5>), sizeof(FftSmem<float, 8, 4>))),
-         cmax(sizeof(FftSmem<float, 9, 3>),
+    cmax(cmax(cmax(sizeof(FftSmem<float, 5, 7, TILE_MID>), sizeof(FftSmem<float, 6, 6, TILE_MID>)),
+              cmax(sizeof(FftSmem<float, 7, 5, TILE_MID>), sizeof(FftSmem<float, 8, 4, TILE_MID>))),
+         cmax(sizeof(FftSmem<float, 9, 3, TILE_MID>),
               cmax(sizeof(SpreadSmem<10>), sizeof(SpreadSmem<11>))));
 
 template <typename T>
@@ -59,18 +60,33 @@ __device__ __forceinline__ int opaque_tid() {
 // turn (4096-element tiles, 2^LOGN rows).  The stages are functions of their
 // own (not inlined), so that each gets the register allocation of its own
 // kernel rather than that of all stages merged.
+template <int LOGN, int KIND>
+__device__ __forceinline__ void slot_tiles(const PersistArgs& a, const FftPassArgs& fa,
+                                          const cplx<float>* in, cplx<float>* out, int p, int c,
+                                          cplx<float>* zpair, unsigned char* smem) {
+  constexpr int LOGT = 12 - LOGN;
+  static_assert(sizeof(FftSmem<float, LOGN, LOGT, KIND>) <= kSmemBytes, "LDS of the largest stage");
+  const int64_t tiles = (a.g.L >> LOGN) >> LOGT;
+  for (int64_t bx = 0; bx < tiles; ++bx) {
+    fft_pass_tile<float, LOGN, LOGT, false, KIND>(
+        fa, in, out, a.mom, a.g, a.tws, (int)bx, p, c, 0, zpair,
+        smem_as<FftSmem<float, LOGN, LOGT, KIND>>(smem), opaque_tid());
+    __syncthreads();  // the next tile rewrites the twiddles and the tile in LDS
+  }
+}
+
 template <int LOGN>
 __device__ __forceinline__ void slot_pass(const PersistArgs& a, const FftPassArgs& fa,
                                           const cplx<float>* in, cplx<float>* out, int p, int c,
                                           cplx<float>* zpair, unsigned char* smem) {
-  constexpr int LOGT = 12 - LOGN;
-  const int64_t tiles = (a.g.L >> LOGN) >> LOGT;
-  for (int64_t bx = 0; bx < tiles; ++bx) {
-    fft_pass_tile<float, LOGN, LOGT, false>(fa, in, out, a.mom, a.g, a.tws, a.twsm, (int)bx, p,
-                                            c, 0, zpair, smem_as<FftSmem<float, LOGN, LOGT>>(smem),
-                                            opaque_tid());
-    __syncthreads();  // the next tile rewrites the twiddles and the tile in LDS
-  }
+  if (fa.kind == PASS_FIRST && fa.np == 2)
+    slot_tiles<LOGN, TILE_FIRST2>(a, fa, in, out, p, c, zpair, smem);
+  else if (fa.kind == PASS_FIRST)
+    slot_tiles<LOGN, TILE_FIRST>(a, fa, in, out, p, c, zpair, smem);
+  else if (fa.kind == PASS_MID)
+    slot_tiles<LOGN, TILE_MID>(a, fa, in, out, p, c, zpair, smem);
+  else
+    slot_tiles<LOGN, TILE_LAST>(a, fa, in, out, p, c, zpair, smem);
 }
 
 template <int LOGB>
