@@ -26,6 +26,7 @@
 // point order, with the same kernel argument (cell - position, exact) as the
 // standalone spreading: the cell values, and so every later result, are the
 // same bit for bit.
+#include <algorithm>
 #include <type_traits>
 
 #include "fchi2_internal.h"
@@ -52,7 +53,7 @@ hipError_t launch_one(const FftPassArgs& a, const void* in, void* out, const Mom
     if (a.fused || a.kind != PASS_SINGLE) return hipErrorInvalidValue;
     launch(std::false_type{}, std::integral_constant<int, TILE_SINGLE>{});
   } else if (a.fused) {
-    if (a.kind != PASS_FIRST || a.mode != MODE_FWD || g.band || (a.np == 2 && !a.tw_tile) || !a.t || !a.x || !a.sigma ||
+    if (a.kind != PASS_FIRST || a.mode != MODE_FWD || g.band || (a.np == 2 && !(a.tw_col && a.tw_row)) || !a.t || !a.x || !a.sigma ||
         !a.tb || (1 << a.tb_log) < g.w + 3)
       return hipErrorInvalidValue;
     if (a.np == 2)
@@ -60,7 +61,7 @@ hipError_t launch_one(const FftPassArgs& a, const void* in, void* out, const Mom
     else
       launch(std::true_type{}, std::integral_constant<int, TILE_FIRST>{});
   } else if (a.kind == PASS_FIRST) {
-    if (a.np == 2 && !a.tw_tile) return hipErrorInvalidValue;
+    if (a.np == 2 && !(a.tw_col && a.tw_row)) return hipErrorInvalidValue;
     if (a.np == 2)
       launch(std::false_type{}, std::integral_constant<int, TILE_FIRST2>{});
     else
@@ -116,7 +117,6 @@ hipError_t dispatch(const FftPassArgs& a, int logn, int logt, const void* in, vo
 
 }  // namespace
 
-int fft_tile_log(bool fp64) { return fp64 ? tile_log_max<double>() : tile_log_max<float>(); }
 
 hipError_t launch_fft_pass(bool fp64, const FftPassArgs& a, int logn, int logt, const void* in,
                            void* out, const Moments* mom, const Geom& g, const void* tws,
@@ -125,10 +125,11 @@ hipError_t launch_fft_pass(bool fp64, const FftPassArgs& a, int logn, int logt, 
   return dispatch<float>(a, logn, logt, in, out, mom, g, tws, n_curves, ncols, st);
 }
 
-hipError_t launch_tile_tw(const void* small, int logn, int logt, void* out, hipStream_t st) {
-  const unsigned n = 1u << (logn + logt);
-  hipLaunchKernelGGL(k_tile_tw, dim3((n + 255) / 256), dim3(256), 0, st, (const C*)small, logn,
-                     logt, (C*)out);
+hipError_t launch_pass2_tw(const void* small, int logn, int logL, void* col, void* row,
+                           hipStream_t st) {
+  const int64_t n = std::max<int64_t>((int64_t)1 << 12, pass2_rows(logn, logL));
+  hipLaunchKernelGGL(k_pass2_tw, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+                     (const C*)small, logn, logL, (C*)col, (C*)row);
   return hipGetLastError();
 }
 

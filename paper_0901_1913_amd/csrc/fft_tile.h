@@ -433,29 +433,47 @@ constexpr bool kind_first(int kind) { return kind == TILE_FIRST || kind == TILE_
 
 // One pass.  Twiddles between passes, for output row k of tile column cc:
 //   PASS_FIRST, np >= 3: w_M^{jd k}        (jd fixed for the tile)   = r[k]
-//   PASS_FIRST, np == 2: w_L^{(g0+cc) k}   = r[k] * small[cc k]
+//   PASS_FIRST, np == 2: w_L^{c k}, c = g0 + cc = G + h  = w_L^{G k} * w_L^{h k}
+//                        (h < TB, G a multiple of TB = 2^12 / N)
 //   PASS_MID:            w_M^{jd (K0+cc+Tail k)}                     = c[cc] r[k]
-// with r, c built per workgroup in FP64 from exactly reduced exponents and
-// small[e] = w_L^e, e < N T, laid out in thread order (tw_tile).
+// with r, c built per workgroup in FP64 from exactly reduced exponents; the two
+// factors of the two-pass form are the plan's (Pass2Tw), so that a tile neither
+// evaluates N sines and cosines nor gathers w_L^{h k} in scattered order.
 //
 // LDS of one tile: the data tile, the stage twiddles (FP32), the row and
 // column twiddles and, in the first pass, the output offset of each tile
 // column.  FP64 tiles keep the row twiddles in the padding column of the data
 // tile (one 16-byte slot per row that no data access touches), which brings
 // the 2^9 x 8 tile from 82 to 74 KB: two workgroups per CU instead of one.
-// The FP32 tile of 2^9 x 16 takes the 80 KB that two workgroups per CU allow.
+// The two-pass first pass of FP32 grids puts its row factors where the stage
+// twiddles were.  The FP32 tile of 2^9 x 16 takes the 80 KB that two workgroups
+// per CU allow.
+//
+// Twiddle factors of the first of two passes with 2^LOGN rows: row[(G / TB) N +
+// k] = w_L^{G k} and col[k TB + h] = w_L^{h k}, in FP64.  The columns of a tile
+// of T = TB or 2 TB columns form G groups, so both tile sizes multiply the same
+// factors.
+template <int LOGN, int LOGT>
+struct Pass2Tw {
+  static constexpr int TB = LOGN < 12 ? 1 << (12 - LOGN) : 1;
+  static constexpr int G = (1 << LOGT) / TB > 0 ? (1 << LOGT) / TB : 1;
+  static constexpr int ROWS = G << LOGN;
+};
+
 template <typename S, int LOGN, int LOGT, int KIND>
 struct FftSmem {
   static constexpr int N = 1 << LOGN;
   static constexpr int T = 1 << LOGT;
   static constexpr int PT = tile_pitch<S, LOGT>();
   static constexpr bool kTrInPad = sizeof(cplx<S>) == sizeof(C) && T > 1;
-  static constexpr bool kTw = kind_first(KIND) || KIND == TILE_MID;
+  static constexpr bool kTw = KIND == TILE_FIRST || KIND == TILE_MID;
+  static constexpr int kSt = StageTw<S, LOGN, LOGT>::SIZE;
+  static constexpr int kRows = KIND == TILE_FIRST2 && !kTrInPad ? Pass2Tw<LOGN, LOGT>::ROWS : 0;
   __align__(16) cplx<S> sm[N * PT];
-  C st[StageTw<S, LOGN, LOGT>::SIZE];
-  C tr[kTw && !kTrInPad ? N : 1];
+  C st[kSt > kRows ? kSt : kRows];
+  C tr[kTw && !kTrInPad ? N : 0];
   // middle pass: column twiddles; first pass: output byte offset of each column
-  C aux[KIND == TILE_MID ? T : (kind_first(KIND) ? (T + 3) / 4 : 1)];
+  C aux[KIND == TILE_MID ? T : (KIND == TILE_FIRST ? (T + 3) / 4 : 0)];
   __device__ __forceinline__ C* tc() { return aux; }
   __device__ __forceinline__ uint32_t* s_rev() { return reinterpret_cast<uint32_t*>(aux); }
   __device__ __forceinline__ C& row_tw(int k) {
@@ -527,6 +545,12 @@ __device__ __forceinline__ void fft_pass_tile(const FftPassArgs& a, const cplx<S
   Tw::fill(sh.st, tw_stage, tid, kNT);
 
   C v[kEPT];
+  using P2 = Pass2Tw<LOGN, LOGT>;
+  constexpr bool F64 = sizeof(S) == 8;
+  static_assert(KIND != TILE_FIRST2 || P2::ROWS <= 2 * kNT, "row factors per thread");
+  // TILE_FIRST2, FP32: row factors on their way to LDS (scalars: a struct copied
+  // from memory to LDS would stay in memory between).
+  double rax = 0.0, ray = 0.0, rbx = 0.0, rby = 0.0;
   // Stage-0 inputs straight from HBM: element i is row b0 + R16 i.
   static_assert(S0::PER == 1, "one radix-16 butterfly per thread in the first stage");
   if constexpr (FIRST || KIND == TILE_SINGLE) {
@@ -548,12 +572,20 @@ __device__ __forceinline__ void fft_pass_tile(const FftPassArgs& a, const cplx<S
 #pragma unroll
       for (int i = 0; i < kEPT; ++i) v[i] = widen(sm[tile_col<S, LOGT>(b0 + i * R16, cc0)]);
     } else {
+      // Loads first, conversions after (the empty asm keeps the compiler from
+      // moving them up): a conversion inside its row's branch would wait for
+      // that one load, sixteen memory latencies in turn.
+      cplx<S> raw[kEPT];
 #pragma unroll
       for (int i = 0; i < kEPT; ++i) {
         const uint32_t r = b0 + i * R16;
-        C val = cmk<double>(0.0, 0.0);
-        if (r < z_lo || r >= z_hi) val = widen(ntl<NT, S>(rb + i * rstep, voff));
-        v[i] = val;
+        raw[i] = cmk<S>((S)0, (S)0);
+        if (r < z_lo || r >= z_hi) raw[i] = ntl<NT, S>(rb + i * rstep, voff);
+      }
+#pragma unroll
+      for (int i = 0; i < kEPT; ++i) {
+        asm("" : "+v"(raw[i].x), "+v"(raw[i].y));
+        v[i] = widen(raw[i]);
       }
     }
   } else {
@@ -570,8 +602,17 @@ __device__ __forceinline__ void fft_pass_tile(const FftPassArgs& a, const cplx<S
     const int64_t Mmask = ((int64_t)1 << logM) - 1;
     for (int k = tid; k < N; k += kNT) sh.row_tw(k) = root((jd * k) & Mmask, logM);
   } else if constexpr (KIND == TILE_FIRST2) {
-    for (int k = tid; k < N; k += kNT)
-      sh.row_tw(k) = root(((int64_t)g0 * k) & ((int64_t)L - 1), logL);
+    const C* rt = (const C*)a.tw_row + ((uint64_t)(g0 / P2::TB) << LOGN);
+    if constexpr (F64) {
+      for (int k = tid; k < N; k += kNT) sh.row_tw(k) = rt[k];
+    } else {
+      rax = rt[tid < P2::ROWS ? tid : 0].x;
+      ray = rt[tid < P2::ROWS ? tid : 0].y;
+      if constexpr (P2::ROWS > kNT) {
+        rbx = rt[tid + kNT].x;
+        rby = rt[tid + kNT].y;
+      }
+    }
   } else if constexpr (KIND == TILE_MID) {
     const int lg = a.logn[a.q - 1];
     const int64_t jd = pre & ((1u << lg) - 1u);
@@ -591,14 +632,31 @@ __device__ __forceinline__ void fft_pass_tile(const FftPassArgs& a, const cplx<S
 #pragma unroll
     for (int j = 0; j < kEPT; ++j) at(j) = cmul_r(at(j), sh.row_tw(b0 + R16 * j));
   } else if constexpr (KIND == TILE_FIRST2) {
-    const C* tt = (const C*)a.tw_tile + tid;
-    constexpr int kGroup = SL::PER > 1 ? 2 : 4;
+    // Entries read ahead: enough to cover the L2's latency, and no more than
+    // the registers of two workgroups per CU allow.
+    constexpr int kAhead = LOGN == 5 || LOGN == 7 ? 2 : 4;
+    const C* tt = (const C*)a.tw_col + (b0 * P2::TB + (cc0 & (P2::TB - 1)));
+    C nx[kAhead];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) nx[j] = tt[j * (R16 * P2::TB)];
+    const C* rw = sh.st + ((cc0 / P2::TB) << LOGN);
+    if constexpr (!F64) {
+      __syncthreads();  // the stage twiddles have been read
+      if (tid < P2::ROWS) sh.st[tid] = cmk<double>(rax, ray);
+      if constexpr (P2::ROWS > kNT) sh.st[tid + kNT] = cmk<double>(rbx, rby);
+      __syncthreads();
+    }
 #pragma unroll
     for (int j = 0; j < kEPT; ++j) {
-      at(j) = cmul_r(at(j), cmul_r(sh.row_tw(b0 + R16 * j), tt[j * kNT]));
-      // All sixteen loads in flight at once would take the registers of two
-      // more workgroups (or spill); a few at a time hide behind the products.
-      if (j % kGroup == kGroup - 1) __builtin_amdgcn_sched_barrier(0);
+      const C t = nx[j % kAhead];
+      if (j + kAhead < kEPT) nx[j % kAhead] = tt[(j + kAhead) * (R16 * P2::TB)];
+      C r;
+      if constexpr (F64)
+        r = sh.row_tw(b0 + R16 * j);
+      else
+        r = rw[b0 + R16 * j];
+      at(j) = cmul_r(at(j), cmul_r(r, t));
+      __builtin_amdgcn_sched_barrier(0);
     }
   } else if constexpr (KIND == TILE_MID) {
     const C fc = sh.tc()[cc0];
@@ -610,20 +668,21 @@ __device__ __forceinline__ void fft_pass_tile(const FftPassArgs& a, const cplx<S
   if constexpr (FIRST) {
     // Transpose through LDS so that each column's N outputs leave as one
     // contiguous run at row rev(c) of the output.
-    const int np = a.np;
-    __syncthreads();
+    if constexpr (KIND == TILE_FIRST || F64) __syncthreads();
 #pragma unroll
     for (int j = 0; j < kEPT; ++j) sm[tile_col<S, LOGT>(b0 + R16 * j, cc0)] = narrow<S>(at(j));
-    // Mixed-radix reversal of each of the tile's T columns, once per tile:
-    // rev = ((j_1 N_2 + j_2) N_3 + j_3) ... + j_{np-1} for column c = g0 + cc.
-    for (int cc = tid; cc < T; cc += kNT) {
-      uint32_t rev = 0, rest = g0 + cc;
-      for (int d = 1; d < np; ++d) {
-        const uint32_t dig = rest & ((1u << a.logn[d]) - 1u);
-        rest >>= a.logn[d];
-        rev = (rev << a.logn[d]) | dig;
+    if constexpr (KIND == TILE_FIRST) {
+      // Mixed-radix reversal of each of the tile's T columns, once per tile:
+      // rev = ((j_1 N_2 + j_2) N_3 + j_3) ... + j_{np-1} for column c = g0 + cc.
+      for (int cc = tid; cc < T; cc += kNT) {
+        uint32_t rev = 0, rest = g0 + cc;
+        for (int d = 1; d < a.np; ++d) {
+          const uint32_t dig = rest & ((1u << a.logn[d]) - 1u);
+          rest >>= a.logn[d];
+          rev = (rev << a.logn[d]) | dig;
+        }
+        sh.s_rev()[cc] = rev * (N * ES);
       }
-      sh.s_rev()[cc] = rev * (N * ES);
     }
     __syncthreads();
 #pragma unroll 4
@@ -631,7 +690,9 @@ __device__ __forceinline__ void fft_pass_tile(const FftPassArgs& a, const cplx<S
       const int e = tid + it * kNT;
       const int k = e & (N - 1);
       const int cc = e >> LOGN;
-      nts<NT, S>(dst, sh.s_rev()[cc] + k * ES, sm[tile_col<S, LOGT>(k, cc)]);
+      // of two passes: rev(c) = c
+      const uint32_t ro = KIND == TILE_FIRST ? sh.s_rev()[cc] : (g0 + cc) * (N * ES);
+      nts<NT, S>(dst, ro + k * ES, sm[tile_col<S, LOGT>(k, cc)]);
     }
   } else if constexpr (KIND == TILE_MID) {
     char* wb = dst + (uint64_t)first * ES;
@@ -639,23 +700,20 @@ __device__ __forceinline__ void fft_pass_tile(const FftPassArgs& a, const cplx<S
     for (int j = 0; j < kEPT; ++j) nts<NT, S>(wb + j * rstep, voff, narrow<S>(at(j)));
   } else if constexpr (KIND == TILE_LAST) {
     // X = g0 + cc + Tail k: bins X < n_freq = L / 4 (rows j < 4) to the direct
-    // half and L - X < n_freq (j >= 12, but for row 12's X = L - n_freq) to the
-    // mirror half, X = 0 to both.
-    char* z0 = (char*)zpair;
-    char* z1 = (char*)(zpair + (L >> 2));
+    // half and bins L - X (rows j >= 12) to the mirror half, where bin k is
+    // element k - 1: a run of columns X, aligned to its length, is then as
+    // aligned in reverse (from element k on, every run of 128 bytes would
+    // leave as a part of two lines).  Row 12's X = L - n_freq fills the mirror
+    // half's unused last element.
+    char* z0 = (char*)zpair + (uint64_t)g0 * ES;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const cplx<S> val = narrow<S>(at(j));
-      nts<false, S>(z0 + (uint64_t)g0 * ES + j * rstep, voff, val);
-      if (j == 0 && bx == 0 && tid == 0) nts<false, S>(z1, 0, val);
-    }
-    // Mirror bin L - X, counted from the tile's row 16 (j + 1) back.
+    for (int j = 0; j < 4; ++j) nts<false, S>(z0 + j * rstep, voff, narrow<S>(at(j)));
+    // Element L - X - 1, counted from the tile's row 16 (j + 1) back.
+    char* z1 = (char*)(zpair + (L >> 2)) - ((int64_t)g0 + 1) * (int64_t)ES;
     const uint32_t moff = (uint32_t)rstep - voff;
 #pragma unroll
-    for (int j = 12; j < kEPT; ++j) {
-      char* zb = z1 + (int64_t)(15 - j) * (int64_t)rstep - (int64_t)g0 * ES;
-      if (j > 12 || bx != 0 || tid != 0) nts<false, S>(zb, moff, narrow<S>(at(j)));
-    }
+    for (int j = 12; j < kEPT; ++j)
+      nts<false, S>(z1 + (15 - j) * (int64_t)rstep, moff, narrow<S>(at(j)));
   } else {
     // PASS_LAST / PASS_SINGLE: X index = K + Tail * k, natural order.
     if (a.mode == MODE_FWD) {
@@ -667,8 +725,8 @@ __device__ __forceinline__ void fft_pass_tile(const FftPassArgs& a, const cplx<S
         const uint32_t X = g0 + cc0 + ((b0 + R16 * j) << logS);
         const cplx<S> val = narrow<S>(at(j));
         if (X < nf) z0[X] = val;
-        const uint32_t Xm = (L - X) & (L - 1);
-        if (Xm < nf) z1[Xm] = val;
+        const uint32_t m1 = L - X - 1;  // mirror bin L - X is element L - X - 1
+        if (m1 < nf) z1[m1] = val;
       }
     } else {
       const uint32_t E = (uint32_t)pair_extent(mo, g, p);
@@ -694,18 +752,17 @@ constexpr int fft_pass_waves() {
   return (sizeof(S) == 4 && !FUSED) ? 4 : 1;
 }
 
-// Thread-order twiddles of the two-pass first pass: out[j NT + tid] =
-// small[cc k] for thread tid's row k = b0 + (N / 16) j of column cc, for a tile
-// of 2^logn rows and 2^logt columns.  The tile's threads read it coalesced;
-// gathered from small[] itself (16 entries of 16 bytes per thread, up to 64
-// cache lines per load) it took most of that pass.
-__global__ void k_tile_tw(const C* __restrict__ small, int logn, int logt, C* __restrict__ out) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= 1 << (logn + logt)) return;
-  const int nt = 1 << (logn + logt - 4);
-  const int tid = e & (nt - 1), j = e / nt;
-  const int cc = tid & ((1 << logt) - 1), k = (tid >> logt) + ((1 << logn) >> 4) * j;
-  out[e] = small[cc * k];
+// The factors of Pass2Tw for rows of 2^logn: col from small[e] = w_L^e, e < 2^12,
+// row from exactly reduced exponents.
+__global__ void k_pass2_tw(const C* __restrict__ small, int logn, int logL, C* __restrict__ col,
+                           C* __restrict__ row) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int logb = 12 - logn;
+  if (e < 1 << 12) col[e] = small[(e & ((1 << logb) - 1)) * (e >> logb)];
+  if (e < ((int64_t)1 << (logL - logb))) {
+    const int64_t G = (e >> logn) << logb, k = e & ((1 << logn) - 1);
+    row[e] = root((G * k) & (((int64_t)1 << logL) - 1), logL);
+  }
 }
 
 // The pass over a wave of curves: grid (column tiles, pairs, curves).

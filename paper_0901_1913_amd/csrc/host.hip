@@ -160,11 +160,11 @@ struct fchi2_plan_s {
   // plan-owned device tables
   int64_t* d_off = nullptr;
   void* d_tw_stage = nullptr;
-  // Thread-order twiddles of the first pass of every two-pass split (see
-  // launch_tile_tw): tiles of 2^le elements with 2^logn rows at
-  // tile_tw_off[le - 12][logn] (SIZE_MAX: no such split).
-  void* d_tw_tile = nullptr;
-  size_t tile_tw_off[2][10];
+  // Twiddle factors of the first pass of every two-pass split, by its rows (see
+  // launch_pass2_tw): byte offsets of the column and row factors of 2^logn rows
+  // (SIZE_MAX: no such split).
+  void* d_pass2 = nullptr;
+  size_t pass2_col[10], pass2_row[10];
   void* d_D = nullptr;
   double* d_gl = nullptr;
   // workspace layout (byte offsets)
@@ -226,11 +226,12 @@ hipError_t prof_mark(fchi2_plan_s* pl, int stage, hipStream_t st) {
     if (pe_ != hipSuccess) return hip_fail(pe_, "profiling event");    \
   } while (0)
 
-// The thread-order twiddles of split f's first pass (null for more than two passes).
-const void* tile_tw(const fchi2_plan_s* pl, const FftPlan& f) {
-  if (f.np != 2) return nullptr;
-  const size_t off = pl->tile_tw_off[f.le[2] - 12][f.logn[2]];
-  return off == SIZE_MAX ? nullptr : (const char*)pl->d_tw_tile + off;
+// The twiddle factors of split f's first pass (two passes only) into a.
+void pass2_tw(const fchi2_plan_s* pl, const FftPlan& f, FftPassArgs& a) {
+  a.tw_col = a.tw_row = nullptr;
+  if (f.np != 2 || pl->pass2_col[f.logn[2]] == SIZE_MAX) return;
+  a.tw_col = (const char*)pl->d_pass2 + pl->pass2_col[f.logn[2]];
+  a.tw_row = (const char*)pl->d_pass2 + pl->pass2_row[f.logn[2]];
 }
 
 // fused_pts: the forward first pass spreads these points (t, x, sigma) in
@@ -286,7 +287,7 @@ fchi2_status_t enqueue_fft(fchi2_plan_s* pl, int mode, void* gA, void* gB, void*
     a.tb = fuse ? fused_tb : nullptr;
     a.tb_log = kFusedTbLog;
     a.ntb = (int)((g.L >> kFusedTbLog) * g.laps) + 2;
-    a.tw_tile = a.kind == PASS_FIRST ? tile_tw(pl, fp) : nullptr;
+    if (a.kind == PASS_FIRST) pass2_tw(pl, fp, a);
     const int logn = fp.logn[q];
     const int logt = fp.le[q] - logn;
     const int64_t ncols = g.L >> logn;
@@ -372,7 +373,7 @@ fchi2_status_t enqueue_persistent(fchi2_plan_s* pl, int cbeg, int cend, const do
     for (int d = 0; d <= kMaxPasses; ++d) f.logn[d] = fp.logn[d];
     f.logL = fp.logL;
     f.curve0 = 0;
-    f.tw_tile = f.kind == PASS_FIRST ? tile_tw(pl, fp) : nullptr;
+    if (f.kind == PASS_FIRST) pass2_tw(pl, fp, f);
   }
   a.fa[0] = a.fa[1];
   a.tws = (const cplx<double>*)pl->d_tw_stage;
@@ -1075,24 +1076,22 @@ fchi2_status_t fchi2_plan(const fchi2_plan_desc_t* desc, void* stream, fchi2_pla
     return alloc_err == hipSuccess;
   };
   const int LT = 1 << kStageLog;
-  const int64_t NSM = (int64_t)1 << fft_tile_log(pl->fp64);
   const int n_gl = 128;
-  // omega_L^e, e < 2^tile, and the thread-order tables made of it.
-  const size_t small_bytes = 16 * (size_t)NSM;
-  size_t tile_tw_bytes = small_bytes;
-  for (auto& row : pl->tile_tw_off)
-    for (size_t& o : row) o = SIZE_MAX;
+  // omega_L^e, e < 2^12, and the two-pass factors made of it.
+  const size_t small_bytes = (size_t)16 << 12;
+  size_t pass2_bytes = small_bytes;
+  for (int ln = 0; ln < 10; ++ln) pl->pass2_col[ln] = pl->pass2_row[ln] = SIZE_MAX;
   for (const FftPlan& f : fft_splits(logL, pl->fp64)) {
-    if (f.np != 2) continue;
-    size_t& o = pl->tile_tw_off[f.le[2] - 12][f.logn[2]];
-    if (o != SIZE_MAX) continue;
-    o = tile_tw_bytes;
-    tile_tw_bytes += (size_t)16 << f.le[2];
+    const int ln = f.logn[2];
+    if (f.np != 2 || pl->pass2_col[ln] != SIZE_MAX) continue;
+    pl->pass2_col[ln] = pass2_bytes;
+    pl->pass2_row[ln] = pass2_bytes + small_bytes;
+    pass2_bytes += small_bytes + 16 * (size_t)pass2_rows(ln, logL);
   }
-  const bool two_pass = tile_tw_bytes > small_bytes;
+  const bool two_pass = pass2_bytes > small_bytes;
   if (!dev_alloc((void**)&pl->d_off, sizeof(int64_t) * (d.n_curves + 1)) ||
       !dev_alloc(&pl->d_tw_stage, 16 * (size_t)LT) ||
-      (two_pass && !dev_alloc(&pl->d_tw_tile, tile_tw_bytes)) ||
+      (two_pass && !dev_alloc(&pl->d_pass2, pass2_bytes)) ||
       !dev_alloc(&pl->d_D, 16 * (size_t)g.n_freq) ||
       !dev_alloc((void**)&pl->d_gl, sizeof(double) * n_gl)) {
     (void)hipGetLastError();
@@ -1103,15 +1102,15 @@ fchi2_status_t fchi2_plan(const fchi2_plan_desc_t* desc, void* stream, fchi2_pla
     return cleanup_fail(hip_fail(alloc_err, "plan table allocation"));
   }
   // FP64 twiddle tables: omega_{2^13}^e and, for two-pass splits, omega_L^e
-  // for e < 2^tile.
-  std::vector<double> hs(2 * (size_t)LT), hsm(two_pass ? 2 * (size_t)NSM : 0);
+  // for e < 2^12.
+  std::vector<double> hs(2 * (size_t)LT), hsm(two_pass ? small_bytes / sizeof(double) : 0);
   auto root = [](int64_t e, int64_t n, double* out2) {
     const long double ang = 2.0L * (long double)M_PI * (long double)(e % n) / (long double)n;
     out2[0] = (double)std::cos(ang);
     out2[1] = (double)std::sin(ang);
   };
   for (int64_t e = 0; e < LT; ++e) root(e, LT, &hs[2 * e]);
-  for (int64_t e = 0; two_pass && e < NSM; ++e) root(e, g.L, &hsm[2 * e]);
+  for (int64_t e = 0; e < (int64_t)hsm.size() / 2; ++e) root(e, g.L, &hsm[2 * e]);
   std::vector<double> gx, gw, gl(n_gl);
   gauss_legendre(n_gl, gx, gw);
   // Positive nodes; weights fold in the kernel value and the factor w.
@@ -1121,15 +1120,14 @@ fchi2_status_t fchi2_plan(const fchi2_plan_desc_t* desc, void* stream, fchi2_pla
     gl[q] = z;
     gl[n_gl / 2 + q] = (double)g.w * gw[n_gl / 2 + q] * phi;
   }
-  auto tile_tables = [&]() -> hipError_t {
-    for (int b = 0; b < 2; ++b)
-      for (int ln = 0; ln < 10; ++ln) {
-        const size_t o = pl->tile_tw_off[b][ln];
-        if (o == SIZE_MAX) continue;
-        const hipError_t r = launch_tile_tw(pl->d_tw_tile, ln, 12 + b - ln,
-                                            (char*)pl->d_tw_tile + o, st);
-        if (r != hipSuccess) return r;
-      }
+  auto pass2_tables = [&]() -> hipError_t {
+    for (int ln = 0; ln < 10; ++ln) {
+      if (pl->pass2_col[ln] == SIZE_MAX) continue;
+      char* base = (char*)pl->d_pass2;
+      const hipError_t r = launch_pass2_tw(base, ln, logL, base + pl->pass2_col[ln],
+                                           base + pl->pass2_row[ln], st);
+      if (r != hipSuccess) return r;
+    }
     return hipSuccess;
   };
   hipError_t e;
@@ -1138,13 +1136,13 @@ fchi2_status_t fchi2_plan(const fchi2_plan_desc_t* desc, void* stream, fchi2_pla
       (e = hipMemcpyAsync(pl->d_tw_stage, hs.data(), sizeof(double) * hs.size(),
                           hipMemcpyHostToDevice, st)) != hipSuccess ||
       (two_pass &&
-       (e = hipMemcpyAsync(pl->d_tw_tile, hsm.data(), small_bytes, hipMemcpyHostToDevice, st)) !=
+       (e = hipMemcpyAsync(pl->d_pass2, hsm.data(), small_bytes, hipMemcpyHostToDevice, st)) !=
            hipSuccess) ||
       (e = hipMemcpyAsync(pl->d_gl, gl.data(), sizeof(double) * n_gl, hipMemcpyHostToDevice,
                           st)) != hipSuccess ||
       (e = launch_deconv_init(pl->d_D, g, pl->d_gl, pl->d_gl + n_gl / 2, n_gl / 2,
                               st)) != hipSuccess ||
-      (e = tile_tables()) != hipSuccess || (e = hipStreamSynchronize(st)) != hipSuccess) {
+      (e = pass2_tables()) != hipSuccess || (e = hipStreamSynchronize(st)) != hipSuccess) {
     return cleanup_fail(hip_fail(e, "plan table setup"));
   }
   // The no-allocation search's device scratch: look up its address on this
@@ -1763,7 +1761,7 @@ void fchi2_destroy(fchi2_plan_t plan) {
   if (plan->gexec) (void)hipGraphExecDestroy(plan->gexec);
   if (plan->d_off) (void)hipFree(plan->d_off);
   if (plan->d_tw_stage) (void)hipFree(plan->d_tw_stage);
-  if (plan->d_tw_tile) (void)hipFree(plan->d_tw_tile);
+  if (plan->d_pass2) (void)hipFree(plan->d_pass2);
   if (plan->d_D) (void)hipFree(plan->d_D);
   if (plan->d_gl) (void)hipFree(plan->d_gl);
   for (hipEvent_t e : {plan->ev_start, plan->ev_spread[0], plan->ev_spread[1], plan->ev_first[0],

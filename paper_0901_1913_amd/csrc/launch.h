@@ -22,7 +22,8 @@ struct FftPassArgs {
   const int32_t* tb;           // fused: tile table of tiles of 2^tb_log cells
   int tb_log;                  //   (2^tb_log >= w + 3), ntb entries per harmonic
   int ntb;
-  const void* tw_tile;         // first pass of two: thread-order twiddles of its tile
+  const void* tw_col;          // first pass of two: its twiddle factors (launch_pass2_tw)
+  const void* tw_row;
 };
 
 // Moments, validity flags and chi2_0 of every curve: bpc workgroups per
@@ -48,15 +49,15 @@ hipError_t launch_tile_bounds(const double* t, const Moments* mom, const Geom& g
                               int n_curves, int64_t max_n, int32_t* tb, int log_tile,
                               hipStream_t st);
 
-// log2 of the elements of the largest FFT tile (rows x columns held in LDS).
-int fft_tile_log(bool fp64);
 // tws: omega_{2^13}^e (FP64).
 hipError_t launch_fft_pass(bool fp64, const FftPassArgs& a, int logn, int logt, const void* in,
                            void* out, const Moments* mom, const Geom& g, const void* tws,
                            int n_curves, int64_t ncols, hipStream_t st);
-// Thread-order twiddles of a two-pass first pass with tiles of 2^logn rows x
-// 2^logt columns, from small[e] = omega_L^e (FP64), e < 2^(logn + logt).
-hipError_t launch_tile_tw(const void* small, int logn, int logt, void* out, hipStream_t st);
+// Twiddle factors of the first of two passes with rows of 2^logn (FP64): col of
+// 2^12 and row of pass2_rows entries, from small[e] = omega_L^e, e < 2^12.
+inline int64_t pass2_rows(int logn, int logL) { return (int64_t)1 << (logL + logn - 12); }
+hipError_t launch_pass2_tw(const void* small, int logn, int logL, void* col, void* row,
+                           hipStream_t st);
 
 // Persistent batched search (MIXED plans, H <= 8, FFT splits of 4096-element
 // tiles with 2^5..2^9 rows per pass, spreading tiles of 2^10 or 2^11 cells):

@@ -178,7 +178,7 @@ __global__ __launch_bounds__(kNT) void k_solve_wide(const cplx<R>* __restrict__ 
   double qr = 0.0, qi = 0.0, pr = 0.0, pi = 0.0;
   auto unpack = [&](int pair, int comp, double& re, double& im) {
     const cplx<R> z0 = zc[(((int64_t)cw * P + pair) * 2 + 0) * nf + k];
-    const cplx<R> z1 = zc[(((int64_t)cw * P + pair) * 2 + 1) * nf + k];
+    const cplx<R> z1 = zc[(((int64_t)cw * P + pair) * 2 + 1) * nf + k - 1];
     double ax, ay;
     if (comp == 0) {
       ax = 0.5 * ((double)z0.x + (double)z1.x);

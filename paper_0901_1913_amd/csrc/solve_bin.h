@@ -32,7 +32,8 @@ struct Layout {
 };
 
 // Unpack pair spectra at bin k into Qr/Qi (m = 0..2H) and Pr/Pi (m = 0..H),
-// already multiplied by the deconvolution / origin-shift factor D[k].
+// already multiplied by the deconvolution / origin-shift factor D[k].  k >= 1;
+// the mirror half holds bin k at element k - 1 (see the last FFT pass).
 template <int H, typename R>
 __device__ __forceinline__ void load_spectra(const cplx<R>* __restrict__ zc, int64_t nf,
                                              int64_t base_pair, int64_t k, cplx<double> Dk_,
@@ -47,7 +48,7 @@ __device__ __forceinline__ void load_spectra(const cplx<R>* __restrict__ zc, int
 #pragma unroll
   for (int pp = 0; pp < P; ++pp) {
     const cplx<R> z0 = zc[((base_pair + pp) * 2 + 0) * nf + k];
-    const cplx<R> z1 = zc[((base_pair + pp) * 2 + 1) * nf + k];
+    const cplx<R> z1 = zc[((base_pair + pp) * 2 + 1) * nf + k - 1];
     const double ax = 0.5 * ((double)z0.x + (double)z1.x);
     const double ay = 0.5 * ((double)z0.y - (double)z1.y);
     const double bx = 0.5 * ((double)z0.y + (double)z1.y);
@@ -94,13 +95,13 @@ __device__ __forceinline__ void load_band(const cplx<R>* __restrict__ zc,
   Pi[0] = 0.0;
 #pragma unroll
   for (int m = 1; m <= 2 * H; ++m) {
-    const cplx<R> z = zc[((base_grid + m - 1) * 2 + half) * nf + j];
+    const cplx<R> z = zc[((base_grid + m - 1) * 2 + half) * nf + j - half];
     Qr[m] = (double)z.x * Dr - (double)z.y * Di;
     Qi[m] = (double)z.x * Di + (double)z.y * Dr;
   }
 #pragma unroll
   for (int m = 1; m <= H; ++m) {
-    const cplx<R> z = zc[((base_grid + 2 * H + m - 1) * 2 + half) * nf + j];
+    const cplx<R> z = zc[((base_grid + 2 * H + m - 1) * 2 + half) * nf + j - half];
     Pr[m] = (double)z.x * Dr - (double)z.y * Di;
     Pi[m] = (double)z.x * Di + (double)z.y * Dr;
   }
@@ -254,7 +255,7 @@ __device__ __forceinline__ void load_q(const cplx<R>* __restrict__ zc, int64_t n
 #pragma unroll
   for (int pp = 0; pp < H; ++pp) {
     const cplx<R> z0 = zc[((base_pair + pp) * 2 + 0) * nf + k];
-    const cplx<R> z1 = zc[((base_pair + pp) * 2 + 1) * nf + k];
+    const cplx<R> z1 = zc[((base_pair + pp) * 2 + 1) * nf + k - 1];
     const double ax = 0.5 * ((double)z0.x + (double)z1.x);
     const double ay = 0.5 * ((double)z0.y - (double)z1.y);
     const double bx = 0.5 * ((double)z0.y + (double)z1.y);
@@ -277,7 +278,7 @@ __device__ __forceinline__ void load_p(const cplx<R>* __restrict__ zc, int64_t n
 #pragma unroll
   for (int j = 0; j < (H + 1) / 2; ++j) {
     const cplx<R> z0 = zc[((base_pair + j) * 2 + 0) * nf + k];
-    const cplx<R> z1 = zc[((base_pair + j) * 2 + 1) * nf + k];
+    const cplx<R> z1 = zc[((base_pair + j) * 2 + 1) * nf + k - 1];
     const double ax = 0.5 * ((double)z0.x + (double)z1.x);
     const double ay = 0.5 * ((double)z0.y - (double)z1.y);
     const double bx = 0.5 * ((double)z0.y + (double)z1.y);
