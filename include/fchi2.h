@@ -99,7 +99,7 @@ typedef enum {
                                       H <= 8, no band, no backward, L =
                                       4 n_freq <= 2^20, FFT passes of
                                       2^12-element tiles with 2^5..2^9 rows,
-                                      spreading tiles of 2^10 or 2^11 cells),
+                                      extents rounded to 2^10 or 2^11 cells),
                                       else ignored; the autotuner may change
                                       it, and times it itself only for
                                       batches with at least as many curves
@@ -464,8 +464,8 @@ fchi2_status_t fchi2_fine_search(fchi2_plan_t plan, const double* t, const doubl
  * Errors: FCHI2_ERR_ARG, FCHI2_ERR_UNSUPPORTED (H > 5), FCHI2_ERR_HIP.
  */
 size_t fchi2_search_multi_workspace_bytes(fchi2_plan_t plan, int32_t n_sources);
-/* The autotuner of fchi2_autotune for this form: times the FFT splits and
- * spreading tiles on fchi2_search_multi with the caller's data (dchi2 is
+/* The autotuner of fchi2_autotune for this form: times the FFT splits
+ * on fchi2_search_multi with the caller's data (dchi2 is
  * scratch) and keeps the fastest in the plan.  Synchronises `stream`. */
 fchi2_status_t fchi2_autotune_multi(fchi2_plan_t plan, const double* t, const double* sigma,
                                     const double* x, const double* scale, int32_t n_sources,
@@ -528,8 +528,8 @@ fchi2_status_t fchi2_profile_read(fchi2_plan_t plan, double* total_ms, int64_t* 
  * Autotuner.  Times every candidate schedule of the plan on the caller's data
  * (the FFT digit splits with the fewest passes and, for grids of at most
  * 2^20 cells, the most balanced splits with one pass more, for FP32 grids each on FFT tiles of 4096 or 8192
- * elements per pass, spreading tiles of 1024 to 8192 cells or, outside band
- * plans, the spreading fused into the first FFT pass, waves of wave_max,
+ * elements per pass, the spreading as a kernel of its own or, outside band
+ * plans, fused into the first FFT pass, waves of wave_max,
  * wave_max/2, /4, /6, /8, /10, /12 curves with the last FFT pass and the
  * solve on whole or half waves, and for batches that fill the device the
  * persistent search; splits and tiles are ranked on the largest wave, wave
@@ -551,7 +551,8 @@ fchi2_status_t fchi2_autotune(fchi2_plan_t plan, const double* t, const double* 
 
 /*
  * Current schedule of a plan: info[0] = FFT passes, info[1..4] = log2 radix of
- * digits 1..4 (0 if unused), info[5] = log2 spreading tile, info[6] = curves
+ * digits 1..4 (0 if unused), info[5] = log2 of the cells to
+ * which the grids' nonzero extents are rounded up (10..13), info[6] = curves
  * per wave, info[7] = kernel width, and with n >= 12 info[8..11] = log2 FFT
  * tile elements of passes 1..4 (0 if unused), with n >= 13 info[12] = 1 if
  * the spreading runs inside the first FFT pass, with n >= 14 info[13] = 1 if
@@ -563,7 +564,7 @@ fchi2_status_t fchi2_plan_info(fchi2_plan_t plan, int32_t* info, int32_t n);
 
 /*
  * Apply a schedule in the layout fchi2_plan_info reports (n >= 14: FFT
- * passes, log2 radices, log2 spreading tile, curves per wave, -, log2 FFT
+ * passes, log2 radices, log2 extent rounding, curves per wave, -, log2 FFT
  * tiles, fused, persistent, and with n >= 15 the last pass's sub-wave, else
  * 0; info[7] is ignored) without timing anything, e.g.
  * one an earlier fchi2_autotune chose, to reproduce a run.  The split must be

@@ -98,7 +98,7 @@ struct Geom {
   int c_off;        // grid origin shift (cells) so that no tap wraps
   int H;            // harmonics
   int P;            // packed complex grids per curve
-  int chunk;        // extents are rounded up to a multiple of this
+  int chunk;        // extents are rounded up to a multiple of this (a power of two)
   int band;         // 1: band plan (first bin k0 > 0, one complex grid per harmonic,
                     //    centred on bin k0 + n_freq / 2)
   int64_t k0;       // first bin of the band (0 for the ordinary search)
@@ -117,7 +117,7 @@ __host__ __device__ inline int64_t pair_extent(const Moments& mo, const Geom& g,
   double pos = ((double)m * v) * (double)g.L + (double)g.c_off;
   int64_t e = (int64_t)pos + (int64_t)(g.w / 2) + 3;
   int64_t c = g.chunk;
-  e = ((e + c - 1) / c) * c;
+  e = (e + c - 1) & -c;
   if (e > g.L) e = g.L;
   return e;
 }

@@ -132,7 +132,7 @@ struct fchi2_plan_s {
   size_t out_elem = 4;    // bytes per Delta chi2 value
   Geom g{};
   FftPlan fp{};
-  int log_tile = 10;
+  int log_tile = 10;  // grid extents are rounded up to 2^log_tile cells
   // Spreading fused into the first FFT pass (no spread grid in memory).
   int fused = 0;
   // Persistent batched search: one launch, curves claimed from a device work
@@ -380,8 +380,7 @@ fchi2_status_t enqueue_persistent(fchi2_plan_s* pl, int cbeg, int cend, const do
   a.D = (const cplx<double>*)pl->d_D;
   a.curve_base = cbeg;
   a.n_curves = cend - cbeg;
-  a.log_tile = pl->log_tile;
-  a.ntb = (int)((pl->g.L >> pl->log_tile) * pl->g.laps) + 2;
+  a.ntb = (int)((pl->g.L >> persist_table_log()) * pl->g.laps) + 2;
   a.slots = ws + pl->off_gA;
   a.slot_bytes = pl->slot_bytes;
   a.off_gB = pl->slot_gB;
@@ -425,7 +424,7 @@ fchi2_status_t enqueue_waves_overlap(fchi2_plan_s* pl, int cbeg, int cend, const
   const bool keep = pl->desc.flags & FCHI2_KEEP_FOR_BACKWARD;
   const size_t zc_curve = (size_t)pl->g.P * 2 * pl->g.n_freq * pl->elem;
   const size_t grid_curve = (size_t)pl->g.P * (size_t)pl->g.L * pl->elem;
-  const size_t tb_half = align256(tile_bounds_bytes(pl->g, pl->log_tile, pl->wave));
+  const size_t tb_half = align256(tile_bounds_bytes(pl->g, kFusedTbLog, pl->wave));
   hipStream_t sd = pl->side;
   hipError_t e = hipEventRecord(pl->ev_start, st);  // moments are done before any spreading
   if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
@@ -443,8 +442,8 @@ fchi2_status_t enqueue_waves_overlap(fchi2_plan_s* pl, int cbeg, int cend, const
       return hip_fail(e, "hipStreamWaitEvent");
     if ((e = prof_mark(pl, FCHI2_PROF_SPREAD, sd)) != hipSuccess)
       return hip_fail(e, "profiling event");
-    e = launch_spread(pl->fp64, t, x, sigma, mom, pl->g, c0, nw, pl->max_n, tb, gA,
-                      pl->log_tile, sd);
+    e = launch_spread(pl->fp64, t, x, sigma, mom, pl->g, c0, nw, pl->max_n, tb,
+                      spread_table_log(pl->g, nw), gA, sd);
     if (e != hipSuccess) return hip_fail(e, "spread");
     if ((e = prof_mark(pl, -1, sd)) != hipSuccess) return hip_fail(e, "profiling event");
     if ((e = hipEventRecord(pl->ev_spread[b], sd)) != hipSuccess)
@@ -503,8 +502,8 @@ fchi2_status_t enqueue_search(fchi2_plan_s* pl, int cbeg, int cend, const double
     int32_t* tb = (int32_t*)(ws + pl->off_tb);
     PROF_BEGIN(FCHI2_PROF_SPREAD);
     if (!use_fused(pl))
-      e = launch_spread(pl->fp64, t, x, sigma, mom, pl->g, c0, nw, pl->max_n, tb, gA,
-                        pl->log_tile, st);
+      e = launch_spread(pl->fp64, t, x, sigma, mom, pl->g, c0, nw, pl->max_n, tb,
+                        spread_table_log(pl->g, nw), gA, st);
     else
       e = launch_tile_bounds(t, mom, pl->g, c0, nw, pl->max_n, tb, kFusedTbLog, st);
     if (e != hipSuccess) return hip_fail(e, "spread");
@@ -572,8 +571,8 @@ fchi2_status_t enqueue_search_top(fchi2_plan_s* pl, const double* t, const doubl
     int32_t* tb = (int32_t*)(ws + pl->off_tb);
     PROF_BEGIN(FCHI2_PROF_SPREAD);
     if (!use_fused(pl))
-      e = launch_spread(pl->fp64, t, x, sigma, mom, pl->g, c0, nw, pl->max_n, tb, gA,
-                        pl->log_tile, st);
+      e = launch_spread(pl->fp64, t, x, sigma, mom, pl->g, c0, nw, pl->max_n, tb,
+                        spread_table_log(pl->g, nw), gA, st);
     else
       e = launch_tile_bounds(t, mom, pl->g, c0, nw, pl->max_n, tb, kFusedTbLog, st);
     if (e != hipSuccess) return hip_fail(e, "spread");
@@ -600,6 +599,7 @@ fchi2_status_t enqueue_search_top(fchi2_plan_s* pl, const double* t, const doubl
 struct MultiLayout {
   Geom gq, gp;
   int wave = 1;
+  int ls = 0;  // strips of the spreading (one tile table serves every source)
   size_t off_mt = 0, off_pt = 0, off_ms = 0, off_ps = 0, off_tb = 0, off_gA = 0, off_gB = 0,
          off_zq = 0, off_zp = 0, bytes = 0;
 };
@@ -622,6 +622,7 @@ MultiLayout multi_layout(const fchi2_plan_s* pl, int S) {
   size_t cap = ((size_t)8 << 30) / (2 * grid_src);
   if (cap < 1) cap = 1;
   m.wave = (int)(cap < (size_t)S ? cap : (size_t)S);
+  m.ls = spread_table_log(m.gp, m.wave);
   const size_t pairs = std::max<size_t>((size_t)pl->g.H, (size_t)m.wave * pd);
   size_t off = 0;
   m.off_mt = off;
@@ -633,7 +634,7 @@ MultiLayout multi_layout(const fchi2_plan_s* pl, int S) {
   m.off_ps = off;
   off = align256(off + sizeof(MomPart) * (size_t)S * pl->mom_bpc);
   m.off_tb = off;
-  off = align256(off + tile_bounds_bytes(pl->g, 10, 1));
+  off = align256(off + tile_bounds_bytes(pl->g, m.ls, 1));
   m.off_gA = off;
   off = align256(off + pairs * (size_t)pl->g.L * pl->elem);
   m.off_gB = off;
@@ -668,7 +669,7 @@ fchi2_status_t enqueue_multi(fchi2_plan_s* pl, const MultiLayout& m, const doubl
   if (e != hipSuccess) return hip_fail(e, "moments");
   PROF_END();
   PROF_BEGIN(FCHI2_PROF_SPREAD);
-  e = launch_spread(pl->fp64, t, x, sigma, mt, m.gq, 0, 1, pl->max_n, tb, gA, pl->log_tile, st);
+  e = launch_spread(pl->fp64, t, x, sigma, mt, m.gq, 0, 1, pl->max_n, tb, m.ls, gA, st);
   if (e != hipSuccess) return hip_fail(e, "spread (weights)");
   PROF_END();
   fchi2_status_t s = enqueue_fft(pl, MODE_FWD, gA, gB, zq, mt, 0, 1, st, &m.gq);
@@ -676,8 +677,8 @@ fchi2_status_t enqueue_multi(fchi2_plan_s* pl, const MultiLayout& m, const doubl
   for (int s0 = 0; s0 < S; s0 += m.wave) {
     const int nw = (S - s0) < m.wave ? (S - s0) : m.wave;
     PROF_BEGIN(FCHI2_PROF_SPREAD);
-    e = launch_spread(pl->fp64, t, x, sigma, ms, m.gp, s0, nw, pl->max_n, tb, gA, pl->log_tile,
-                      st, true);
+    e = launch_spread(pl->fp64, t, x, sigma, ms, m.gp, s0, nw, pl->max_n, tb, m.ls, gA, st,
+                      true);
     if (e != hipSuccess) return hip_fail(e, "spread (sources)");
     PROF_END();
     s = enqueue_fft(pl, MODE_FWD, gA, gB, zp, ms, s0, nw, st, &m.gp);
@@ -699,9 +700,9 @@ fchi2_status_t check_ws(fchi2_plan_s* pl, void* ws, size_t bytes) {
   return FCHI2_OK;
 }
 
-// Schedule search with `run`.  Stage 1 times every (FFT split, spreading
-// tile) on the largest wave (plus the fused first pass and the persistent
-// search where allowed); stage 2 times, for the fastest candidate of each of
+// Schedule search with `run`.  Stage 1 times every FFT split on the largest wave
+// (plus the fused first pass and the persistent search where allowed); stage 2
+// times, for the fastest candidate of each of
 // the three fastest FFT splits of stage 1 (the best wave size differs between
 // splits: their passes share the CUs differently with the overlapped
 // spreading), every wave size, each with the last pass and solve run on the
@@ -761,13 +762,11 @@ fchi2_status_t tune_loop(fchi2_plan_s* pl, const std::vector<FftPlan>& splits,
   std::vector<TuneCand> cands;
   const int w0 = waves[0];
   for (const FftPlan& f : splits) {
-    for (int tile : {10, 11, 12, 13}) cands.push_back(TuneCand{f, tile, w0, 0, 0, 0, 1e30f});
-    // The fused schedule has no spreading tile.
+    cands.push_back(TuneCand{f, 10, w0, 0, 0, 0, 1e30f});
     if (allow_fused && f.np >= 2) cands.push_back(TuneCand{f, 10, w0, 1, 0, 0, 1e30f});
     // The persistent search has no waves.
-    for (int tile : {10, 11})
-      if (allow_persist && persist_ok(pl, f, tile) && persist_worth_timing(pl))
-        cands.push_back(TuneCand{f, tile, w0, 0, 1, 0, 1e30f});
+    if (allow_persist && persist_ok(pl, f, 10) && persist_worth_timing(pl))
+      cands.push_back(TuneCand{f, 10, w0, 0, 1, 0, 1e30f});
   }
   time_all(cands);
   if (res == FCHI2_OK && !cands.empty()) {
@@ -1053,7 +1052,7 @@ fchi2_status_t fchi2_plan(const fchi2_plan_desc_t* desc, void* stream, fchi2_pla
       pl->slot_gB = align256(grid1);
       pl->slot_zc = pl->slot_gB + align256(grid1);
       pl->slot_tb = pl->slot_zc + align256(zc_curve);
-      pl->slot_bytes = align256(pl->slot_tb + tile_bounds_bytes(g, 10, 1));
+      pl->slot_bytes = align256(pl->slot_tb + tile_bounds_bytes(g, persist_table_log(), 1));
       const size_t room = pl->off_queue - pl->off_gA;
       int64_t n = (int64_t)cus * per_cu;
       pl->n_slots_device = (int)n;

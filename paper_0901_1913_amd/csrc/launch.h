@@ -37,11 +37,13 @@ hipError_t launch_moments(const double* t, const double* x, const double* sigma,
                           bool shared_t = false, const double* scale = nullptr);
 
 // Spread w and w*(x - xbar) of each curve of the wave onto its P packed grids.
-// tb: tile -> point-range table, tile_bounds_bytes(g, log_tile, n_curves).
+// tb: tile -> point-range table, tile_bounds_bytes(g, ls, n_curves), with
+// ls = spread_table_log(g, n_curves).
 hipError_t launch_spread(bool fp64, const double* t, const double* x, const double* sigma,
                          const Moments* mom, const Geom& g, int curve0, int n_curves,
-                         int64_t max_n, int32_t* tb, void* grid, int log_tile, hipStream_t st,
+                         int64_t max_n, int32_t* tb, int ls, void* grid, hipStream_t st,
                          bool share_tb = false);
+int spread_table_log(const Geom& g, int n_curves);
 size_t tile_bounds_bytes(const Geom& g, int log_tile, int n_curves);
 // The tile table alone (tiles of 2^log_tile cells): the fused first FFT pass
 // reads it to find each row segment's points.
@@ -79,7 +81,6 @@ struct PersistArgs {
   const cplx<double>* D;
   int curve_base;
   int n_curves;
-  int log_tile;
   int ntb;
   char* slots;
   size_t slot_bytes, off_gB, off_zc, off_tb;
@@ -88,6 +89,7 @@ struct PersistArgs {
   float* out;
   uint8_t* flags;
 };
+int persist_table_log();  // granularity of a slot's tile table
 size_t persist_smem_bytes();
 hipError_t persist_occupancy(int H, int* blocks_per_cu);
 hipError_t launch_persistent(const PersistArgs& a, int n_slots, hipStream_t st);

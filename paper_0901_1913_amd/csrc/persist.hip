@@ -30,14 +30,16 @@ constexpr size_t cmax(T a, T b) {
   return a > b ? a : b;
 }
 
+constexpr int kSlotLS = kStripLogMax;  // strips of the spreading
+using SlotSpread = SpreadSmem<kSlotLS, false>;
+
 // LDS of the largest stage: FFT tiles of 4096 FP32 elements (N = 2^5..2^9
-// rows; the middle pass's hold the most) and spreading tiles of 1024 or 2048
-// cells.
+// rows; the middle pass's hold the most) and the spreading of four waves.
 constexpr size_t kSmemBytes =
     cmax(cmax(cmax(sizeof(FftSmem<float, 5, 7, TILE_MID>), sizeof(FftSmem<float, 6, 6, TILE_MID>)),
               cmax(sizeof(FftSmem<float, 7, 5, TILE_MID>), sizeof(FftSmem<float, 8, 4, TILE_MID>))),
          cmax(sizeof(FftSmem<float, 9, 3, TILE_MID>),
-              cmax(sizeof(SpreadSmem<10>), sizeof(SpreadSmem<11>))));
+              sizeof(SlotSpread[kNT / 64])));
 
 template <typename T>
 __device__ __forceinline__ T& smem_as(unsigned char* p) {
@@ -89,21 +91,22 @@ __device__ __forceinline__ void slot_pass(const PersistArgs& a, const FftPassArg
     slot_tiles<LOGN, TILE_LAST>(a, fa, in, out, p, c, zpair, smem);
 }
 
-template <int LOGB>
 __device__ __forceinline__ void slot_spread(const PersistArgs& a, const Moments& mo, int p,
                                             const int32_t* tb, cplx<float>* gA,
                                             unsigned char* smem) {
-  const int64_t nt = pair_extent(mo, a.g, p) >> LOGB;
-  for (int64_t tile = 0; tile < nt; ++tile)
-    spread_tile<float, LOGB, false>(a.t, a.x, a.sigma, mo, a.g, 0, tb, a.ntb, 0, p, tile,
-                                    gA + (tile << LOGB), smem_as<SpreadSmem<LOGB>>(smem), opaque_tid());
+  const int n = (int)(pair_extent(mo, a.g, p) / SlotSpread::kCells);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  SlotSpread& sh = smem_as<SlotSpread[kNT / 64]>(smem)[wave];
+  for (int item = wave; item < n; item += kNT / 64)
+    spread_strips<float, kSlotLS, false>(a.t, a.x, a.sigma, mo, a.g, tb, a.ntb, p, item * spread_strips_per_wave(false),
+                                gA + (int64_t)item * SlotSpread::kCells, sh, opaque_tid() & 63);
 }
 
 template <int H>
 __device__ __forceinline__ void slot_tables(const PersistArgs& a, const Moments& mo, int32_t* tb) {
   for (int m = 1; m <= 2 * a.g.H; ++m)
     for (int64_t il = opaque_tid(); il <= mo.n; il += kNT)
-      tile_bounds_point(a.t, mo, a.g, 0, m, il, a.log_tile, a.ntb, tb);
+      tile_bounds_point(a.t, mo, a.g, 0, m, il, kSlotLS, a.ntb, tb);
 }
 
 template <int H>
@@ -151,10 +154,7 @@ __global__ __launch_bounds__(kNT, persist_waves<H>()) void k_search_persistent(P
       slot_tables<H>(a, mo, tb);
       __syncthreads();
       for (int p = 0; p < g.P; ++p) {
-        if (a.log_tile == 10)
-          slot_spread<10>(a, mo, p, tb, gA, smem);
-        else
-          slot_spread<11>(a, mo, p, tb, gA, smem);
+        slot_spread(a, mo, p, tb, gA, smem);
         __syncthreads();
         for (int q = a.fa[1].np; q >= 1; --q) {
           const FftPassArgs& fa = a.fa[q];
@@ -180,6 +180,8 @@ __global__ __launch_bounds__(kNT, persist_waves<H>()) void k_search_persistent(P
 __global__ void k_queue_reset(int* next) { *next = 0; }
 
 }  // namespace
+
+int persist_table_log() { return kSlotLS; }
 
 size_t persist_smem_bytes() { return kSmemBytes; }
 

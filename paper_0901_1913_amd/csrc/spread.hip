@@ -17,9 +17,9 @@
 // ("lap") of the grid; the tile table runs over the plan's laps.
 //
 // Two real grids are packed per complex grid (real part, imaginary part);
-// each workgroup owns a tile of cells of one packed grid and sums the kernel
-// contributions of its points cell by cell (deterministic, no atomics).  The
-// arithmetic is FP64 (for float grids the kernel's exponential is taken to
+// each wave owns strips of consecutive cells of one packed grid and sums the
+// kernel contributions of their points tap by tap, every cell in point order
+// (deterministic, no atomics).  The arithmetic is FP64 (for float grids the kernel's exponential is taken to
 // FP32 accuracy, see es_kernel.h); the grid is stored as S (float for mixed
 // plans).
 #include <algorithm>
@@ -195,10 +195,10 @@ __global__ __launch_bounds__(kNT) void k_tile_bounds(const double* __restrict__ 
   tile_bounds_point(t, mo, g, cw, m, il, log_tile, ntb, tb);
 }
 
-// Blocks of one curve (wave slot blockIdx.z) stride over the tiles below each
-// pair's nonzero extent, pair after pair (cells beyond the extent are never
+// The waves of one curve (wave slot blockIdx.y) stride over the strips below
+// each pair's nonzero extent, pair after pair (cells beyond the extent are never
 // read).
-template <typename S, int LOGB, bool BAND>
+template <typename S, int LS, bool BAND>
 __global__ __launch_bounds__(kNT) void k_spread(const double* __restrict__ t,
                                                 const double* __restrict__ x,
                                                 const double* __restrict__ sigma,
@@ -206,23 +206,24 @@ __global__ __launch_bounds__(kNT) void k_spread(const double* __restrict__ t,
                                                 int curve0, const int32_t* __restrict__ tb,
                                                 int ntb, int share_tb,
                                                 cplx<S>* __restrict__ grid) {
-  __shared__ SpreadSmem<LOGB> sh;
-  const int cw = blockIdx.z;
+  constexpr int kWaveCells = SpreadSmem<LS, BAND>::kCells;
+  __shared__ SpreadSmem<LS, BAND> sh[kNT / 64];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63;
+  const int cw = blockIdx.y;
   const Moments mo = mom[curve0 + cw];
   if (mo.flags & kCurveFatal) return;
-  int64_t items = 0;
-  for (int q = 0; q < g.P; ++q) items += pair_extent(mo, g, q) >> LOGB;
-  for (int64_t wi = blockIdx.x; wi < items; wi += gridDim.x) {
-    int p = 0;
-    int64_t tile = wi;
-    for (;;) {
-      const int64_t nt = pair_extent(mo, g, p) >> LOGB;
-      if (tile < nt) break;
-      tile -= nt;
-      ++p;
-    }
-    spread_tile<S, LOGB, BAND>(t, x, sigma, mo, g, cw, tb, ntb, share_tb, p, tile,
-                               grid + ((int64_t)cw * g.P + p) * g.L + (tile << LOGB), sh, threadIdx.x);
+  const int32_t* rows = tb + (share_tb ? 0 : (int64_t)cw * (2 * g.H) * ntb);
+  const int step = gridDim.x * (kNT / 64);
+  int item = blockIdx.x * (kNT / 64) + wave;
+  for (int p = 0; p < g.P; ++p) {
+    const int n = (int)(pair_extent(mo, g, p) / kWaveCells);
+    for (; item < n; item += step)
+      spread_strips<S, LS, BAND>(t, x, sigma, mo, g, rows, ntb, p,
+                                 item * spread_strips_per_wave(BAND),
+                             grid + ((int64_t)cw * g.P + p) * g.L + (int64_t)item * kWaveCells,
+                             sh[wave], lane);
+    item -= n;
   }
 }
 
@@ -264,43 +265,48 @@ hipError_t launch_moments(const double* t, const double* x, const double* sigma,
 
 hipError_t launch_spread(bool fp64, const double* t, const double* x, const double* sigma,
                          const Moments* mom, const Geom& g, int curve0, int n_curves,
-                         int64_t max_n, int32_t* tb, void* grid, int log_tile, hipStream_t st,
+                         int64_t max_n, int32_t* tb, int ls, void* grid, hipStream_t st,
                          bool share_tb) {
-  const int64_t tiles = g.L >> log_tile;
-  const int ntb = (int)(tiles * g.laps) + 2;
-  dim3 gb((unsigned)((max_n + 1 + kNT - 1) / kNT), (unsigned)(2 * g.H), (unsigned)n_curves);
+  if (ls != kStripLogMin && ls != kStripLogMax) return hipErrorInvalidValue;
   // Sources sharing one time base share the table of slot 0 (built already).
-  if (!share_tb)
-    hipLaunchKernelGGL(k_tile_bounds, gb, dim3(kNT), 0, st, t, mom, g, curve0, log_tile, ntb,
-                       tb);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  // Blocks stride over the non-empty tiles of each curve (counted on the device).
-  const int64_t cap = std::max<int64_t>(8, 4096 / std::max(n_curves, 1));
-  dim3 gr((unsigned)std::min<int64_t>(cap, tiles * g.P), 1u, (unsigned)n_curves);
-  auto launch_b = [&](auto logb, auto band) -> void {
-    constexpr int LB = decltype(logb)::value;
-    constexpr bool BD = decltype(band)::value;
-    if (fp64)
-      hipLaunchKernelGGL((k_spread<double, LB, BD>), gr, dim3(kNT), 0, st, t, x, sigma, mom, g,
-                         curve0, tb, ntb, share_tb ? 1 : 0, (cplx<double>*)grid);
-    else
-      hipLaunchKernelGGL((k_spread<float, LB, BD>), gr, dim3(kNT), 0, st, t, x, sigma, mom, g,
-                         curve0, tb, ntb, share_tb ? 1 : 0, (cplx<float>*)grid);
-  };
-  auto launch = [&](auto logb) -> void {
-    if (g.band)
-      launch_b(logb, std::true_type{});
-    else
-      launch_b(logb, std::false_type{});
-  };
-  switch (log_tile) {
-    case 10: launch(std::integral_constant<int, 10>{}); break;
-    case 11: launch(std::integral_constant<int, 11>{}); break;
-    case 12: launch(std::integral_constant<int, 12>{}); break;
-    case 13: launch(std::integral_constant<int, 13>{}); break;
-    default: return hipErrorInvalidValue;
+  if (!share_tb) {
+    hipError_t e = launch_tile_bounds(t, mom, g, curve0, n_curves, max_n, tb, ls, st);
+    if (e != hipSuccess) return e;
   }
+  const int ntb = (int)((g.L >> ls) * g.laps) + 2;
+  // Waves stride over the non-empty strips of each curve (counted on the
+  // device).  A few curves: no more waves than about three rounds of the
+  // device, an empty wave costs a launch (one curve of 2e4 points, H = 4, 2^20
+  // bins: 38 us with 4096 blocks, 49 with 16384).  Many: shorter shares, so that
+  // uneven curves balance (1001 curves of 2^16 bins: 1.07 ms with 16384, 1.19
+  // with 4096).
+  const int64_t most = ((g.L >> ls) / 2 * g.P + kNT / 64 - 1) / (kNT / 64);
+  const int64_t blocks = n_curves < 32 ? 4096 : 16384;
+  const int64_t per = std::max<int64_t>(8, blocks / std::max(n_curves, 1));
+  dim3 gr((unsigned)std::min(most, per), (unsigned)n_curves);
+  auto launch = [&](auto elem, auto strip, auto band) -> void {
+    using S = decltype(elem);
+    constexpr int LS = decltype(strip)::value;
+    constexpr bool BD = decltype(band)::value;
+    hipLaunchKernelGGL((k_spread<S, LS, BD>), gr, dim3(kNT), 0, st, t, x, sigma, mom, g, curve0,
+                       tb, ntb, share_tb ? 1 : 0, (cplx<S>*)grid);
+  };
+  auto by_band = [&](auto elem, auto strip) {
+    if (g.band)
+      launch(elem, strip, std::true_type{});
+    else
+      launch(elem, strip, std::false_type{});
+  };
+  auto by_strip = [&](auto elem) {
+    if (ls == kStripLogMin)
+      by_band(elem, std::integral_constant<int, kStripLogMin>{});
+    else
+      by_band(elem, std::integral_constant<int, kStripLogMax>{});
+  };
+  if (fp64)
+    by_strip(double{});
+  else
+    by_strip(float{});
   return hipGetLastError();
 }
 
@@ -311,6 +317,16 @@ hipError_t launch_tile_bounds(const double* t, const Moments* mom, const Geom& g
   dim3 gb((unsigned)((max_n + 1 + kNT - 1) / kNT), (unsigned)(2 * g.H), (unsigned)n_curves);
   hipLaunchKernelGGL(k_tile_bounds, gb, dim3(kNT), 0, st, t, mom, g, curve0, log_tile, ntb, tb);
   return hipGetLastError();
+}
+
+// Strips of 32 cells where all grids together hold fewer than 20000 waves'
+// worth of 128-cell strips (four a wave): there the longest sequence of points
+// in one strip decides (150 points on 2^10 bins: 14 against 22 us; 1000 points,
+// FP64, 2^14 bins: 17 against 24; 3 curves of H = 12 on 2^15 bins: 52 against
+// 63), elsewhere the points shared by neighbouring strips do (2e4 points, H = 4,
+// 2^20 bins: 55 against 38 us; 1e5 points, 2^22 bins: 262 against 187).
+int spread_table_log(const Geom& g, int n_curves) {
+  return (g.L >> 9) * g.P * n_curves < 20000 ? kStripLogMin : kStripLogMax;
 }
 
 size_t tile_bounds_bytes(const Geom& g, int log_tile, int n_curves) {
