@@ -140,7 +140,7 @@ def stage_roofline(cur, stages, steps_profiled, b, o, schedule):
 _FFT_SRC = ["fft.hip", "fft_tile.h"]
 STAGE_SOURCES = {
     "fft_first": _FFT_SRC, "fft_mid": _FFT_SRC, "fft_last": _FFT_SRC,
-    "solve": ["solve.hip", "solve_bin.h"],
+    "solve": ["solve.hip", "solve_wide.hip", "solve_bin.h"],
     "spread": ["spread.hip", "spread_tile.h", "es_kernel.h"],
     "persistent": ["persist.hip", "fft_tile.h", "spread_tile.h", "solve_bin.h"],
 }

@@ -71,7 +71,7 @@ typedef enum {
 /* Plan flags. */
 #define FCHI2_KEEP_FOR_BACKWARD 1u /* keep all spectra in the workspace      */
 #define FCHI2_GRAPH 2u             /* replay searches through a HIP graph    */
-#define FCHI2_WIDE_SOLVE 8u        /* solve every bin with the wave-per-bin
+#define FCHI2_WIDE_SOLVE 8u        /* solve every bin with the sixteen-lane
                                       solver (automatic for H > 8); same
                                       results as the register solver; no
                                       backward or band plans                 */

@@ -10,7 +10,7 @@
 namespace fchi2 {
 
 constexpr int kHMax = 8;            // harmonics supported by the register solver
-constexpr int kHWide = 16;          // harmonics supported by the wave-per-bin solver
+constexpr int kHWide = 16;          // harmonics supported by the sixteen-lane solver
 constexpr int kMaxPairs = 24;       // 3 * kHMax (band plans: one grid per harmonic),
                                     // = kHWide + kHWide / 2 packed pairs
 constexpr int kMaxPasses = 4;       // FFT passes (digits of the grid length)

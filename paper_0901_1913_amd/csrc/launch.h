@@ -102,11 +102,16 @@ hipError_t launch_deconv_init(void* D, const Geom& g, const double* gl_x, const 
 // Normal-matrix assembly, Cholesky and prefix Delta chi2 per bin; coef
 // (nullable): the H model's coefficients [curve][2H+1][n_freq], output type.
 // H <= 8 uses the register solver (one bin per thread) unless `wide`; H > 8
-// always the wave-per-bin solver (H <= 16, not for band plans).
+// always the sixteen-lane solver (H <= 16, not for band plans).
 hipError_t launch_solve(bool fp64, const void* zc, const void* D, const Moments* mom,
                         const Geom& g, int curve0, int n_curves, double eps_piv, void* dchi2,
                         uint8_t* flags, hipStream_t st, void* coef = nullptr,
                         bool wide = false);
+
+// Sixteen lanes per bin, any H <= 16 (launch_solve picks it; not for band plans).
+hipError_t launch_solve_wide(bool fp64, const void* zc, const void* D, const Moments* mom,
+                             const Geom& g, int curve0, int n_curves, double eps, void* out,
+                             uint8_t* flags, void* coef, hipStream_t st);
 
 // Shared-alpha solve for sources at the same times (H <= 5): alpha from the
 // weight spectra zq (slot 0, H pairs), beta per source from zp (ceil(H/2)
