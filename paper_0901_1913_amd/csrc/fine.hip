@@ -13,11 +13,12 @@
 // search; the coefficients solve L^T A = z (eq. eqcoeffs) and xbar is added
 // back to A_0.
 //
-// Phase 1 (k_fine_sums): a block holds 256 trial frequencies of one curve and
+// Phase 1 (k_fine_sums): a wave holds 64 trial frequencies of one curve and
 // one chunk of its points; the points are staged through LDS and every
 // thread accumulates the 3H complex sums of its frequency.  Partial sums go
-// to scratch, per chunk.  Phase 2 (k_fine_solve): one block per candidate
-// adds the chunks in order (deterministic), solves every trial frequency and
+// to scratch, per chunk.  Phase 2 (k_fine_reduce): a thread per sum adds the
+// chunks in order (deterministic) into the first chunk's place.  Phase 3
+// (k_fine_solve): one block per candidate solves every trial frequency and
 // keeps the best one of row hrow (ties to the lower index).
 #include <cmath>
 #include <cstdint>
@@ -40,21 +41,71 @@ __device__ __forceinline__ double fine_freq(double fc, double hw, int r, int R) 
   return R > 1 ? fc + hw * (2.0 * (double)r / (double)(R - 1) - 1.0) : fc;
 }
 
+// Adds U consecutive points, in order, to the sums of trial frequency f.
+template <int H, int U>
+__device__ __forceinline__ void fine_points(const double* tau, const double* w,
+                                            const double* wy, double f, double (&acc)[6 * H]) {
+  double cs[U], sn[U], zr[U], zi[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const double cyc = f * tau[u];
+    // f tau - floor(f tau) in one FMA: the product's rounding stays out
+    const double fr = __builtin_fma(f, tau[u], -floor(cyc));
+    sincospi(2.0 * fr, &sn[u], &cs[u]);
+    zr[u] = cs[u];
+    zi[u] = sn[u];
+  }
+  static_for<1, 2 * H + 1>([&](auto mc) {
+    constexpr int mm = decltype(mc)::value;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if constexpr (mm == 2) {
+        const double p = cs[u] * sn[u];
+        zr[u] = __builtin_fma(cs[u], cs[u], -(sn[u] * sn[u]));
+        zi[u] = p + p;
+      } else if constexpr (mm > 2) {
+        const double nr = __builtin_fma(zr[u], cs[u], -(zi[u] * sn[u]));
+        zi[u] = __builtin_fma(zi[u], cs[u], zr[u] * sn[u]);
+        zr[u] = nr;
+      }
+      acc[2 * (mm - 1)] = __builtin_fma(w[u], zr[u], acc[2 * (mm - 1)]);
+      acc[2 * (mm - 1) + 1] = __builtin_fma(w[u], zi[u], acc[2 * (mm - 1) + 1]);
+      if constexpr (mm <= H) {
+        constexpr int p = 4 * H + 2 * (mm - 1);
+        acc[p] = __builtin_fma(wy[u], zr[u], acc[p]);
+        acc[p + 1] = __builtin_fma(wy[u], zi[u], acc[p + 1]);
+      }
+    }
+  });
+}
+
+// FP64 arithmetic bounds it (about 130 vector instructions a point at H = 5).
+// A wave is its own workgroup: with 256 threads, lists of fewer trial
+// frequencies left whole waves of every workgroup idle, always on the same
+// SIMDs.  Two points at a time hide one point's chain of dependent FMAs behind
+// the other's, since a launch holds only one or two waves a SIMD (1e5 points,
+// 1024 trial frequencies: 98 chunks x 16 waves on 1024 SIMDs); the next points
+// are loaded while these are summed.  Three levels of 16 x 64 trials on 1e5
+// points, H = 5: 1894 us before, 1465 now (with the chunks added by their own
+// kernel); one wave a SIMD already runs at the two-wave rate, and what is left
+// is that 1568 waves on 1024 SIMDs take the time of 2048.
+constexpr int kWave = 64;
+
 template <int H>
-__global__ __launch_bounds__(kNT) void k_fine_sums(const double* __restrict__ t,
-                                                   const double* __restrict__ x,
-                                                   const double* __restrict__ sigma,
-                                                   const Moments* __restrict__ mom,
-                                                   const double* __restrict__ fc, int K, int R,
-                                                   double hw, int n_chunks,
-                                                   double* __restrict__ part) {
+__global__ __launch_bounds__(kWave) void k_fine_sums(const double* __restrict__ t,
+                                                     const double* __restrict__ x,
+                                                     const double* __restrict__ sigma,
+                                                     const Moments* __restrict__ mom,
+                                                     const double* __restrict__ fc, int K, int R,
+                                                     double hw, int n_chunks,
+                                                     double* __restrict__ part) {
   constexpr int NC = 6 * H;  // Re/Im of Q_1..Q_2H and P_1..P_H
-  __shared__ double s_tau[kNT], s_w[kNT], s_wy[kNT];
+  __shared__ double s_tau[kWave], s_w[kWave], s_wy[kWave];
   const int tid = threadIdx.x;
   const int c = blockIdx.z;
   const int chunk = blockIdx.y;
   const int KR = K * R;
-  const int q = blockIdx.x * kNT + tid;
+  const int q = blockIdx.x * kWave + tid;
   const Moments mo = mom[c];
   const int64_t p0 = (int64_t)chunk * kChunk;
   if (p0 >= mo.n && chunk > 0) return;  // this curve has no such chunk
@@ -70,42 +121,28 @@ __global__ __launch_bounds__(kNT) void k_fine_sums(const double* __restrict__ t,
 #pragma unroll
   for (int j = 0; j < NC; ++j) acc[j] = 0.0;
 
-  for (int64_t b = p0; b < p1; b += kNT) {
-    const int64_t i = b + tid;
-    if (i < p1) {
-      const int64_t gi = mo.start + i;
-      const double s = sigma[gi];
-      const double w = 1.0 / (s * s);
-      s_tau[tid] = t[gi] - mo.T0;
-      s_w[tid] = w;
-      s_wy[tid] = w * (x[gi] - mo.xbar);
+  double nt = 0.0, nx = 0.0, ns = 1.0;  // the next points, on their way
+  auto fetch = [&](int64_t b) {
+    if (b + tid < p1) {
+      const int64_t gi = mo.start + b + tid;
+      nt = t[gi];
+      nx = x[gi];
+      ns = sigma[gi];
     }
+  };
+  fetch(p0);
+  for (int64_t b = p0; b < p1; b += kWave) {
+    const double w = 1.0 / (ns * ns);
+    s_tau[tid] = nt - mo.T0;
+    s_w[tid] = w;
+    s_wy[tid] = w * (nx - mo.xbar);
     __syncthreads();
-    const int m = (p1 - b) < kNT ? (int)(p1 - b) : kNT;
+    fetch(b + kWave);
+    const int m = (p1 - b) < kWave ? (int)(p1 - b) : kWave;
     if (active) {
-      for (int j = 0; j < m; ++j) {
-        const double cyc = f * s_tau[j];
-        const double fr = cyc - floor(cyc);
-        double sn, cs;
-        sincospi(2.0 * fr, &sn, &cs);
-        const double w = s_w[j], wy = s_wy[j];
-        double zr = cs, zi = sn;
-        static_for<1, 2 * H + 1>([&](auto mc) {
-          constexpr int mm = decltype(mc)::value;
-          if constexpr (mm > 1) {
-            const double nr = zr * cs - zi * sn;
-            const double ni = zr * sn + zi * cs;
-            zr = nr;
-            zi = ni;
-          }
-          acc[2 * (mm - 1)] += w * zr;
-          acc[2 * (mm - 1) + 1] += w * zi;
-          if constexpr (mm <= H) {
-            acc[4 * H + 2 * (mm - 1)] += wy * zr;
-            acc[4 * H + 2 * (mm - 1) + 1] += wy * zi;
-          }
-        });
-      }
+      int j = 0;
+      for (; j + 2 <= m; j += 2) fine_points<H, 2>(s_tau + j, s_w + j, s_wy + j, f, acc);
+      if (j < m) fine_points<H, 1>(s_tau + j, s_w + j, s_wy + j, f, acc);
     }
     __syncthreads();
   }
@@ -116,20 +153,44 @@ __global__ __launch_bounds__(kNT) void k_fine_sums(const double* __restrict__ t,
   }
 }
 
-// Spectra of trial frequency q of curve c: chunk partial sums added in order.
+// part[c][0][i] = sum over the curve's chunks of part[c][chunk][i], in order, i
+// any of the NC KR sums: a chain of loads as long as the chunks, bound by their
+// latency, eight in flight.  (The solve kernel adding them itself, K workgroups
+// with 6H such chains a thread, took 105 us a call for 98 chunks of 1024 trials,
+// H = 5; this takes 7 and the solve another 7.)
+__global__ __launch_bounds__(kWave) void k_fine_reduce(const Moments* __restrict__ mom,
+                                                       int n_chunks, int64_t sums,
+                                                       double* part) {
+  const int c = blockIdx.y;
+  const int64_t i = (int64_t)blockIdx.x * kWave + threadIdx.x;
+  const Moments& mo = mom[c];
+  if (i >= sums || (mo.flags & kCurveFatal)) return;
+  const int used = (int)((mo.n + kChunk - 1) / kChunk);
+  if (used < 2) return;
+  double* p = part + (int64_t)c * n_chunks * sums + i;
+  double acc = 0.0;
+  int ch = 0;
+  for (; ch + 8 <= used; ch += 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = p[(int64_t)(ch + u) * sums];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc += v[u];
+  }
+  for (; ch < used; ++ch) acc += p[(int64_t)ch * sums];
+  p[0] = acc;
+}
+
+// Spectra of trial frequency q of curve c from its sums.
 template <int H>
 __device__ __forceinline__ void fine_spectra(const double* __restrict__ part, int64_t c,
-                                             int n_chunks, int used, int KR, int q, double W,
+                                             int n_chunks, int KR, int q, double W,
                                              double* Qr, double* Qi, double* Pr, double* Pi) {
   constexpr int NC = 6 * H;
   double acc[NC];
+  const double* p = part + c * n_chunks * NC * KR + q;
 #pragma unroll
-  for (int j = 0; j < NC; ++j) acc[j] = 0.0;
-  for (int ch = 0; ch < used; ++ch) {
-    const double* p = part + (c * n_chunks + ch) * NC * KR + q;
-#pragma unroll
-    for (int j = 0; j < NC; ++j) acc[j] += p[(int64_t)j * KR];
-  }
+  for (int j = 0; j < NC; ++j) acc[j] = p[(int64_t)j * KR];
   Qr[0] = W;
   Qi[0] = 0.0;
   Pr[0] = 0.0;
@@ -162,7 +223,6 @@ __global__ __launch_bounds__(kNT) void k_fine_solve(
   const int KR = K * R;
   const Moments mo = mom[c];
   const bool fatal = (mo.flags & kCurveFatal) != 0;
-  const int used = fatal ? 0 : (int)((mo.n + kChunk - 1) / kChunk);
   const double fcen = fc[(int64_t)c * K + cand];
   const bool cand_ok = !fatal && fcen > 0.0 && isfinite(fcen);
   const int64_t o = (int64_t)c * K + cand;
@@ -174,7 +234,7 @@ __global__ __launch_bounds__(kNT) void k_fine_solve(
     double d[H];
     if (cand_ok && f > 0.0 && isfinite(f)) {
       double Qr[2 * H + 1], Qi[2 * H + 1], Pr[H + 1], Pi[H + 1];
-      fine_spectra<H>(part, c, n_chunks, used, KR, cand * R + r, mo.W, Qr, Qi, Pr, Pi);
+      fine_spectra<H>(part, c, n_chunks, KR, cand * R + r, mo.W, Qr, Qi, Pr, Pi);
       uint8_t fl = 0;
       double Lm[dd][dd], inv[dd], z[dd];
       prefix_solve<H, double>(Qr, Qi, Pr, Pi, kEps, d, fl, Lm, inv, z);
@@ -224,7 +284,7 @@ __global__ __launch_bounds__(kNT) void k_fine_solve(
   // leaving its A at 0; xbar added back to A_0.
   const double f = fine_freq(fcen, hw, win, R);
   double Qr[2 * H + 1], Qi[2 * H + 1], Pr[H + 1], Pi[H + 1];
-  fine_spectra<H>(part, c, n_chunks, used, KR, cand * R + win, mo.W, Qr, Qi, Pr, Pi);
+  fine_spectra<H>(part, c, n_chunks, KR, cand * R + win, mo.W, Qr, Qi, Pr, Pi);
   uint8_t fl = 0;
   if (mo.span > 0.0 && f * mo.span < 1.0) fl |= BF_LOW_F;
   double d[H];
@@ -254,11 +314,18 @@ template <int H>
 hipError_t fine_h(const double* t, const double* x, const double* sigma, const Moments* mom,
                   int n_curves, const double* fc, int K, int R, double hw, int n_chunks,
                   double* part, int hrow, const FineOut& out, hipStream_t st) {
-  dim3 g1((unsigned)((K * R + kNT - 1) / kNT), (unsigned)n_chunks, (unsigned)n_curves);
-  hipLaunchKernelGGL((k_fine_sums<H>), g1, dim3(kNT), 0, st, t, x, sigma, mom, fc, K, R, hw,
+  dim3 g1((unsigned)((K * R + kWave - 1) / kWave), (unsigned)n_chunks, (unsigned)n_curves);
+  hipLaunchKernelGGL((k_fine_sums<H>), g1, dim3(kWave), 0, st, t, x, sigma, mom, fc, K, R, hw,
                      n_chunks, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (n_chunks > 1) {
+    const int64_t sums = (int64_t)6 * H * K * R;
+    dim3 gr((unsigned)((sums + kWave - 1) / kWave), (unsigned)n_curves);
+    hipLaunchKernelGGL(k_fine_reduce, gr, dim3(kWave), 0, st, mom, n_chunks, sums, part);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   dim3 g2((unsigned)K, (unsigned)n_curves);
   hipLaunchKernelGGL((k_fine_solve<H>), g2, dim3(kNT), 0, st, mom, fc, K, R, hw, n_chunks,
                      (const double*)part, hrow, out.rows, out.f_best, out.dchi2_best, out.coef,
