@@ -558,7 +558,9 @@ fchi2_status_t fchi2_autotune(fchi2_plan_t plan, const double* t, const double* 
  * the spreading runs inside the first FFT pass, with n >= 14 info[13] = 1 if
  * searches run as one persistent launch, with n >= 15 info[14] = curves per
  * launch of the last FFT pass and the solve (0: the whole wave).  n must be
- * >= 8.
+ * >= 8.  A plan whose schedule has neither been tuned nor set reports tiles of
+ * 2^12 and runs those or, in FP32, 2^13, whichever suits each launch's size
+ * (the same results); tuning or setting a schedule fixes them.
  */
 fchi2_status_t fchi2_plan_info(fchi2_plan_t plan, int32_t* info, int32_t n);
 

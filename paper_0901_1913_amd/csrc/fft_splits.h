@@ -138,20 +138,52 @@ inline std::vector<FftPlan> fft_splits_uniform(int logL, int LE) {
   return out;
 }
 
-// Whether every pass q of the split fits its tile of 2^le[q] elements: the
-// T = 2^(le[q] - logn[q]) columns of a tile must share their other digits.
+// Whether pass q of the split can take tiles of 2^le elements: the
+// T = 2^(le - logn[q]) columns of a tile must share their other digits.
+inline bool pass_tile_valid(const FftPlan& f, int q, int le) {
+  const int logt = le - f.logn[q];
+  if (logt < 0) return false;
+  if (q == f.np) return logt <= f.logn[1];          // first pass
+  if (q == 1) return logt <= f.logL - f.logn[1];    // last pass
+  int tail = 0;                                     // middle passes
+  for (int d = q + 1; d <= f.np; ++d) tail += f.logn[d];
+  return logt <= tail;
+}
+
+// Whether every pass q of the split fits its tile of 2^le[q] elements.
 inline bool split_valid(const FftPlan& f) {
   if (f.np == 1) return true;
-  const int np = f.np;
-  for (int q = 1; q <= np; ++q)
-    if (f.le[q] - f.logn[q] < 0) return false;
-  if (f.le[np] - f.logn[np] > f.logn[1]) return false;  // first pass
-  for (int q = 2; q < np; ++q) {                          // middle passes
-    int tail = 0;
-    for (int d = q + 1; d <= np; ++d) tail += f.logn[d];
-    if (f.le[q] - f.logn[q] > tail) return false;
-  }
-  return f.le[1] - f.logn[1] <= f.logL - f.logn[1];      // last pass
+  for (int q = 1; q <= f.np; ++q)
+    if (!pass_tile_valid(f, q, f.le[q])) return false;
+  return true;
+}
+
+// log2 of the tile of pass q for a launch over `grids` FP32 grids, where
+// neither the autotuner nor the caller has chosen one (the results are the same
+// bits).  Tiles of 2^13 elements move runs twice as long, but halve the
+// workgroups and leave two of 64 KB per compute unit instead of four, so they
+// pay where runs are short (a radix of 2^9 leaves 64 bytes on 2^12 elements)
+// and where many workgroups follow each other.  Time on 2^12 over time on 2^13,
+// by tiles of 2^13 in the launch (H = 3 and 6, 1..200 curves, 2^12..2^22 bins):
+//   first pass, radix 2^9: 160: 1.08, 288: 1.08, 2304: 1.09, 18432: 1.26;
+//     2^8: 640..4608: 0.86..0.98, from 8000 with mostly empty grids 0.95..1.03
+//     and with full ones 1.16 (16384 and more); 2^7 and less: 0.85..1.09, below
+//     1 on most;
+//   middle pass: 1280: 1.09, 2560: 1.03, 3840: 1.09, 10240 and more: 1.1..1.16;
+//   last pass, 2^9: 80: 0.90, 144: 1.08, 240: 1.06, 1280: 1.30, 5120: 1.43;
+//     2^8: 576: 0.95, 864: 1.16, 2304: 1.18, 14400: 1.12;
+//     2^7: 1152: 0.96, 1280: 1.02, 2000: 1.05, 7200: 1.11.
+inline int launch_tile_log(const FftPlan& f, int q, int64_t grids) {
+  const int64_t tiles = (grids << f.logL) >> 13;
+  const int n = f.logn[q];
+  bool pays;
+  if (q == f.np)
+    pays = n == 9 ? tiles >= 160 : n == 8 && tiles >= 8192;
+  else if (q > 1)
+    pays = tiles >= 1024;
+  else
+    pays = tiles >= (n == 9 ? 128 : n == 8 ? 768 : 1536);
+  return f.np > 1 && pays && pass_tile_valid(f, q, 13) ? 13 : f.le[q];
 }
 
 // Autotuner candidates: the splits of fft_splits_uniform for 2^12-element

@@ -132,6 +132,9 @@ struct fchi2_plan_s {
   size_t out_elem = 4;    // bytes per Delta chi2 value
   Geom g{};
   FftPlan fp{};
+  // Whether the caller or the autotuner chose fp's tiles; else launch_tile_log
+  // does, by the size of each launch.
+  bool tiles_chosen = false;
   int log_tile = 10;  // grid extents are rounded up to 2^log_tile cells
   // Spreading fused into the first FFT pass (no spread grid in memory).
   int fused = 0;
@@ -195,6 +198,7 @@ namespace {
 
 void apply_fft_plan(fchi2_plan_s* pl, const FftPlan& f) {
   pl->fp = f;
+  pl->tiles_chosen = true;
   const int64_t S_first = (f.np == 1) ? 1 : (pl->g.L >> f.logn[f.np]);
   const int64_t tile = (int64_t)1 << pl->log_tile;
   pl->g.chunk = (int)(S_first > tile ? S_first : tile);
@@ -289,7 +293,8 @@ fchi2_status_t enqueue_fft(fchi2_plan_s* pl, int mode, void* gA, void* gB, void*
     a.ntb = (int)((g.L >> kFusedTbLog) * g.laps) + 2;
     if (a.kind == PASS_FIRST) pass2_tw(pl, fp, a);
     const int logn = fp.logn[q];
-    const int logt = fp.le[q] - logn;
+    const bool by_size = !pl->tiles_chosen && !pl->fp64 && !fuse;
+    const int logt = (by_size ? launch_tile_log(fp, q, (int64_t)g.P * nw) : fp.le[q]) - logn;
     const int64_t ncols = g.L >> logn;
     const void* in = (q == fp.np) ? gA : gB;
     void* out = gB;
@@ -989,6 +994,7 @@ fchi2_status_t fchi2_plan(const fchi2_plan_desc_t* desc, void* stream, fchi2_pla
   pl->fused = (d.flags & FCHI2_FUSED_SPREAD) ? 1 : 0;
   pl->persist = (d.flags & FCHI2_PERSISTENT) ? 1 : 0;
   apply_fft_plan(pl, pl->fp);
+  pl->tiles_chosen = false;
 
   // Waves: bound the two grid buffers to ~8 GiB unless the caller chose.
   const size_t grid_curve = (size_t)g.P * (size_t)g.L * pl->elem;
@@ -1522,7 +1528,7 @@ fchi2_status_t fchi2_autotune_multi(fchi2_plan_t plan, const double* t, const do
   }
   const std::vector<FftPlan> splits = fft_splits(pl->fp.logL, pl->fp64);
   const std::vector<int> waves = {pl->wave};
-  const bool prof = pl->prof;
+  const bool prof = pl->prof, chosen = pl->tiles_chosen;
   pl->prof = false;
   float best_ms = 1e30f;
   TuneCand best{pl->fp, pl->log_tile, pl->wave, pl->fused, pl->persist, pl->solve_sub, 0.f};
@@ -1535,6 +1541,7 @@ fchi2_status_t fchi2_autotune_multi(fchi2_plan_t plan, const double* t, const do
       st, best_ms, best);
   pl->prof = prof;
   apply_tuned(pl, best);
+  if (best_ms == 1e30f) pl->tiles_chosen = chosen;  // nothing was timed
   pl->last_ws = nullptr;
   ++pl->gen;
   return res;
@@ -1667,7 +1674,7 @@ fchi2_status_t fchi2_autotune(fchi2_plan_t plan, const double* t, const double* 
       const int w = pl->wave_max / div;
       if (w >= 1 && w != waves.back()) waves.push_back(w);
     }
-  const bool prof = pl->prof;
+  const bool prof = pl->prof, chosen = pl->tiles_chosen;
   pl->prof = false;
   float best_ms = 1e30f;
   TuneCand best{pl->fp, pl->log_tile, pl->wave, pl->fused, pl->persist, pl->solve_sub, 0.f};
@@ -1681,6 +1688,7 @@ fchi2_status_t fchi2_autotune(fchi2_plan_t plan, const double* t, const double* 
       st, best_ms, best);
   pl->prof = prof;
   apply_tuned(pl, best);
+  if (best_ms == 1e30f) pl->tiles_chosen = chosen;  // nothing was timed
   const FftPlan& best_f = best.f;
   pl->last_ws = nullptr;
   ++pl->gen;
