@@ -62,6 +62,12 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
+// Lane N's value of each row of sixteen lanes (every lane active).
+template <int N>
+__device__ __forceinline__ double row_bcast(double v) {
+  return __builtin_amdgcn_update_dpp(v, v, 0x150 + N, 0xf, 0xf, true);
+}
+
 template <typename R>
 struct cplx {
   R x, y;

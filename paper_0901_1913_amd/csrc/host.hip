@@ -448,7 +448,7 @@ fchi2_status_t enqueue_waves_overlap(fchi2_plan_s* pl, int cbeg, int cend, const
     if ((e = prof_mark(pl, FCHI2_PROF_SPREAD, sd)) != hipSuccess)
       return hip_fail(e, "profiling event");
     e = launch_spread(pl->fp64, t, x, sigma, mom, pl->g, c0, nw, pl->max_n, tb,
-                      spread_table_log(pl->g, nw), gA, sd);
+                      spread_table_log(pl->g, nw, pl->max_n), gA, sd);
     if (e != hipSuccess) return hip_fail(e, "spread");
     if ((e = prof_mark(pl, -1, sd)) != hipSuccess) return hip_fail(e, "profiling event");
     if ((e = hipEventRecord(pl->ev_spread[b], sd)) != hipSuccess)
@@ -508,7 +508,7 @@ fchi2_status_t enqueue_search(fchi2_plan_s* pl, int cbeg, int cend, const double
     PROF_BEGIN(FCHI2_PROF_SPREAD);
     if (!use_fused(pl))
       e = launch_spread(pl->fp64, t, x, sigma, mom, pl->g, c0, nw, pl->max_n, tb,
-                        spread_table_log(pl->g, nw), gA, st);
+                        spread_table_log(pl->g, nw, pl->max_n), gA, st);
     else
       e = launch_tile_bounds(t, mom, pl->g, c0, nw, pl->max_n, tb, kFusedTbLog, st);
     if (e != hipSuccess) return hip_fail(e, "spread");
@@ -577,7 +577,7 @@ fchi2_status_t enqueue_search_top(fchi2_plan_s* pl, const double* t, const doubl
     PROF_BEGIN(FCHI2_PROF_SPREAD);
     if (!use_fused(pl))
       e = launch_spread(pl->fp64, t, x, sigma, mom, pl->g, c0, nw, pl->max_n, tb,
-                        spread_table_log(pl->g, nw), gA, st);
+                        spread_table_log(pl->g, nw, pl->max_n), gA, st);
     else
       e = launch_tile_bounds(t, mom, pl->g, c0, nw, pl->max_n, tb, kFusedTbLog, st);
     if (e != hipSuccess) return hip_fail(e, "spread");
@@ -627,7 +627,7 @@ MultiLayout multi_layout(const fchi2_plan_s* pl, int S) {
   size_t cap = ((size_t)8 << 30) / (2 * grid_src);
   if (cap < 1) cap = 1;
   m.wave = (int)(cap < (size_t)S ? cap : (size_t)S);
-  m.ls = spread_table_log(m.gp, m.wave);
+  m.ls = spread_table_log(m.gp, m.wave, pl->max_n);
   const size_t pairs = std::max<size_t>((size_t)pl->g.H, (size_t)m.wave * pd);
   size_t off = 0;
   m.off_mt = off;

@@ -36,12 +36,6 @@ using namespace solve_detail;
 // and rows move in runs of sixteen.  DM: rows a build is unrolled for (d <= DM).
 constexpr int kWideBins = kNT / 16;
 
-// Lane N's value of each row of sixteen lanes (every lane active).
-template <int N>
-__device__ __forceinline__ double row_bcast(double v) {
-  return __builtin_amdgcn_update_dpp(v, v, 0x150 + N, 0xf, 0xf, true);
-}
-
 // v plus its value in another lane of the row (a DPP control without a bank or
 // row mask; every lane active).
 template <int CTRL>

@@ -197,7 +197,11 @@ __global__ __launch_bounds__(kNT) void k_tile_bounds(const double* __restrict__ 
 
 // The waves of one curve (wave slot blockIdx.y) stride over the strips below
 // each pair's nonzero extent, pair after pair (cells beyond the extent are never
-// read).
+// read).  A curve that covers little of its grids has its points in the first
+// strips of each pair, so each curve starts at another workgroup: workgroup ids
+// go round the eight XCDs, and a stride that is a multiple of eight gave every
+// curve's full strips to the same one (20 curves of 1280 points, H = 4, 2^11
+// bins, a fifth of the grids covered: 145 against 92 us).
 template <typename S, int LS, bool BAND>
 __global__ __launch_bounds__(kNT) void k_spread(const double* __restrict__ t,
                                                 const double* __restrict__ x,
@@ -215,7 +219,7 @@ __global__ __launch_bounds__(kNT) void k_spread(const double* __restrict__ t,
   if (mo.flags & kCurveFatal) return;
   const int32_t* rows = tb + (share_tb ? 0 : (int64_t)cw * (2 * g.H) * ntb);
   const int step = gridDim.x * (kNT / 64);
-  int item = blockIdx.x * (kNT / 64) + wave;
+  int item = (blockIdx.x + 3 * cw) % gridDim.x * (kNT / 64) + wave;
   for (int p = 0; p < g.P; ++p) {
     const int n = (int)(pair_extent(mo, g, p) / kWaveCells);
     for (; item < n; item += step)
@@ -324,9 +328,15 @@ hipError_t launch_tile_bounds(const double* t, const Moments* mom, const Geom& g
 // in one strip decides (150 points on 2^10 bins: 14 against 22 us; 1000 points,
 // FP64, 2^14 bins: 17 against 24; 3 curves of H = 12 on 2^15 bins: 52 against
 // 63), elsewhere the points shared by neighbouring strips do (2e4 points, H = 4,
-// 2^20 bins: 55 against 38 us; 1e5 points, 2^22 bins: 262 against 187).
-int spread_table_log(const Geom& g, int n_curves) {
-  return (g.L >> 9) * g.P * n_curves < 20000 ? kStripLogMin : kStripLogMax;
+// 2^20 bins: 55 against 38 us; 1e5 points, 2^22 bins: 262 against 187).  Up to
+// 65536 the sequences still decide where a strip of 128 holds four points or
+// more on average (150 curves of 1280 points, H = 4, 2^13 bins, the harmonics
+// over 7, 20 and 70 % of the grid: 186, 168 and 203 us against 253, 171 and 150;
+// 20 curves of 20480 points, 2^15 bins: 351, 293 and 288 against 647, 344 and 263).
+int spread_table_log(const Geom& g, int n_curves, int64_t max_n) {
+  const int64_t waves = (g.L >> 9) * g.P * n_curves;
+  const bool dense = max_n * 128 >= 4 * g.L;
+  return waves < (dense ? 65536 : 20000) ? kStripLogMin : kStripLogMax;
 }
 
 size_t tile_bounds_bytes(const Geom& g, int log_tile, int n_curves) {
