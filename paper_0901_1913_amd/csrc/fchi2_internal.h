@@ -68,6 +68,14 @@ __device__ __forceinline__ double row_bcast(double v) {
   return __builtin_amdgcn_update_dpp(v, v, 0x150 + N, 0xf, 0xf, true);
 }
 
+// v of another lane of the row, by a DPP control without masks (every lane active).
+template <int CTRL>
+__device__ __forceinline__ double row_move(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
 template <typename R>
 struct cplx {
   R x, y;

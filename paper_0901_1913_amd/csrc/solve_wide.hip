@@ -36,15 +36,6 @@ using namespace solve_detail;
 // and rows move in runs of sixteen.  DM: rows a build is unrolled for (d <= DM).
 constexpr int kWideBins = kNT / 16;
 
-// v plus its value in another lane of the row (a DPP control without a bank or
-// row mask; every lane active).
-template <int CTRL>
-__device__ __forceinline__ double row_add(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
-  return v + __hiloint2double(hi, lo);
-}
-
 template <bool COEF, int DM>
 __global__ __launch_bounds__(kNT) void k_solve_wide(const void* __restrict__ zc,
                                                     const cplx<double>* __restrict__ D,
@@ -243,10 +234,10 @@ __global__ __launch_bounds__(kNT) void k_solve_wide(const void* __restrict__ zc,
         p[q] = r + 16 * q > j ? a[q][j] * A[q] : 0.0;
       });
       double sum = (p[0] + p[2]) + (p[1] + p[3]);
-      sum = row_add<0x128>(sum);  // lane ^ 8 (row_ror 8)
-      sum = row_add<0x124>(sum);  // lane ^ 4 (row_ror 4: lanes l and l ^ 8 are equal)
-      sum = row_add<0x4E>(sum);   // lane ^ 2 (quad_perm)
-      sum = row_add<0xB1>(sum);   // lane ^ 1
+      sum += row_move<0x128>(sum);  // lane ^ 8 (row_ror 8)
+      sum += row_move<0x124>(sum);  // lane ^ 4 (row_ror 4: lanes l and l ^ 8 are equal)
+      sum += row_move<0x4E>(sum);   // lane ^ 2 (quad_perm)
+      sum += row_move<0xB1>(sum);   // lane ^ 1
       if (r == j % 16) A[j / 16] = (z_own[j / 16] - sum) * inv_own[j / 16];
       __builtin_amdgcn_sched_barrier(0);
     });

@@ -197,16 +197,14 @@ __device__ __forceinline__ void spread_strips(const double* __restrict__ t,
       // Four points at a time: their taps do not depend on each other, only
       // the sums do.
       constexpr int kU = 4;
-      static_for<0, 16 / kU>([&](auto kc) {
-        constexpr int k = kU * decltype(kc)::value;
-        if (!__any(k < cnt)) return;
+      for (int k = 0; __any(k < cnt); k += kU) {
         double phi[kU], vr[kU], vi[kU];
         int j[kU];
         static_for<0, kU>([&](auto uc) {
           constexpr int u = decltype(uc)::value;
-          const double rel = row_bcast<k + u>(q.rel);
-          vr[u] = row_bcast<k + u>(q.re);
-          vi[u] = BAND ? row_bcast<k + u>(q.im) : 0.0;
+          const double rel = row_bcast<u>(q.rel);
+          vr[u] = row_bcast<u>(q.re);
+          vi[u] = BAND ? row_bcast<u>(q.im) : 0.0;
           const int f = (int)floor(k + u < cnt ? rel : 0.0) - 7;
           j[u] = f + ((r - f) & 15);
           phi[u] = es_kernel<EXACT>(((double)j[u] - rel) * two_over_w, beta);
@@ -227,7 +225,11 @@ __device__ __forceinline__ void spread_strips(const double* __restrict__ t,
             if constexpr (BAND) acc_i = fma(phi[u], vi[u], acc_i);
           }
         }
-      });
+        // the next four to the row's first lanes (row_ror 12: from lane r + 4)
+        q.rel = row_move<0x12C>(q.rel);
+        q.re = row_move<0x12C>(q.re);
+        if constexpr (BAND) q.im = row_move<0x12C>(q.im);
+      }
     }
     flush();
     __builtin_amdgcn_wave_barrier();
