@@ -50,61 +50,6 @@ __device__ __forceinline__ T block_sum(T v, T* red) {
   return r;
 }
 
-// Phase 1: block b of curve c reduces a contiguous chunk of the curve to
-// (W_b, mean_b, M2_b = sum w (x - mean_b)^2) and validity bits.  With
-// shared_t every curve c uses the points [off[0], off[1]) of t and sigma and
-// its own data x[c * n + i] (sources observed at the same times).
-__global__ __launch_bounds__(kNT) void k_moments_part(const double* __restrict__ t,
-                                                      const double* __restrict__ x,
-                                                      const double* __restrict__ sigma,
-                                                      const int64_t* __restrict__ off,
-                                                      int bpc, int shared_t,
-                                                      MomPart* __restrict__ part) {
-  __shared__ double red[kNT / 64];
-  __shared__ uint32_t bad_s;
-  const int c = blockIdx.y;
-  const int b = blockIdx.x;
-  const int tid = threadIdx.x;
-  const int64_t a = shared_t ? off[0] : off[c], e = shared_t ? off[1] : off[c + 1];
-  const int64_t xs = shared_t ? (int64_t)c * (e - a) : 0;
-  const int64_t n = e - a;
-  const int64_t chunk = (n + bpc - 1) / bpc;
-  const int64_t lo = a + (int64_t)b * chunk;
-  const int64_t hi = (lo + chunk < e) ? lo + chunk : e;
-  if (tid == 0) bad_s = 0;
-  __syncthreads();
-  double sw = 0.0, swx = 0.0;
-  uint32_t bad = 0;
-  for (int64_t i = lo + tid; i < hi; i += kNT) {
-    const double ti = t[i], xi = x[i + xs], si = sigma[i];
-    if (!isfinite(ti) || !isfinite(xi) || !isfinite(si) || !(si > 0.0)) bad |= CF_NONFINITE;
-    if (i > a && !(ti >= t[i - 1])) bad |= CF_UNSORTED;
-    const double w = 1.0 / (si * si);
-    sw += w;
-    swx += w * xi;
-  }
-  if (bad) atomicOr(&bad_s, bad);
-  const double W = block_sum(sw, red);
-  const double WX = block_sum(swx, red);
-  const double mean = (W > 0.0) ? WX / W : 0.0;
-  double sc = 0.0;
-  for (int64_t i = lo + tid; i < hi; i += kNT) {
-    const double si = sigma[i];
-    const double y = x[i + xs] - mean;
-    sc += y * y / (si * si);
-  }
-  const double M2 = block_sum(sc, red);
-  if (tid == 0) {
-    MomPart pp;
-    pp.W = W;
-    pp.mean = mean;
-    pp.M2 = M2;
-    pp.bad = bad_s;
-    pp.pad = 0;
-    part[(int64_t)c * bpc + b] = pp;
-  }
-}
-
 // Pairwise combination of two chunk summaries (parallel variance update);
 // an empty chunk (W = 0) leaves the other unchanged.
 __device__ __forceinline__ void mom_combine(double& W, double& mean, double& M2, double W2,
@@ -117,34 +62,13 @@ __device__ __forceinline__ void mom_combine(double& W, double& mean, double& M2,
   W = Wn;
 }
 
-// Phase 2: one wave per curve.  Lane j combines chunks j, j + 64, ... in
-// order, then the 64 lane summaries are combined by a fixed pairwise tree
-// (deterministic); lane 0 writes the curve's Moments and chi2_0.
-__global__ __launch_bounds__(64) void k_moments_fin(const double* __restrict__ t,
-                                                    const int64_t* __restrict__ off,
-                                                    int n_curves, int bpc, int shared_t,
-                                                    const double* __restrict__ scale,
-                                                    const MomPart* __restrict__ part, Geom g,
-                                                    Moments* __restrict__ mom,
-                                                    double* __restrict__ chi2_out) {
-  const int c = blockIdx.x;
-  const int lane = threadIdx.x;
-  double W = 0.0, mean = 0.0, M2 = 0.0;
-  uint32_t fl = 0;
-  for (int b = lane; b < bpc; b += 64) {
-    const MomPart pp = part[(int64_t)c * bpc + b];
-    fl |= pp.bad;
-    mom_combine(W, mean, M2, pp.W, pp.mean, pp.M2);
-  }
-  for (int o = 1; o < 64; o <<= 1) {
-    const double W2 = __shfl_down(W, o), mean2 = __shfl_down(mean, o), M22 = __shfl_down(M2, o);
-    const uint32_t f2 = (uint32_t)__shfl_down((int)fl, o);
-    if ((lane & (2 * o - 1)) == 0) {
-      mom_combine(W, mean, M2, W2, mean2, M22);
-      fl |= f2;
-    }
-  }
-  if (lane != 0) return;
+// The curve's Moments and chi2_0 from its summary.
+__device__ __forceinline__ void moments_write(const double* __restrict__ t,
+                                              const int64_t* __restrict__ off, int c,
+                                              int shared_t, const double* __restrict__ scale,
+                                              const Geom& g, double W, double mean, double M2,
+                                              uint32_t fl, Moments* __restrict__ mom,
+                                              double* __restrict__ chi2_out) {
   const int64_t a = shared_t ? off[0] : off[c], e = shared_t ? off[1] : off[c + 1];
   const int64_t n = e - a;
   Moments m;
@@ -181,6 +105,104 @@ __global__ __launch_bounds__(64) void k_moments_fin(const double* __restrict__ t
   m.pad = 0;
   mom[c] = m;
   if (chi2_out) chi2_out[c] = (fl & kCurveFatal) ? NAN : M2 / sc2;
+}
+
+// Phase 1: block b of curve c reduces a contiguous chunk of the curve to
+// (W_b, mean_b, M2_b = sum w (x - mean_b)^2) and validity bits.  With
+// shared_t every curve c uses the points [off[0], off[1]) of t and sigma and
+// its own data x[c * n + i] (sources observed at the same times).  ONE: a curve
+// is one chunk, and its block writes the result (a launch less: 1000 points,
+// FP64, 2^14 bins, 35.7 against 33.8 us).
+template <bool ONE>
+__global__ __launch_bounds__(kNT) void k_moments_part(const double* __restrict__ t,
+                                                      const double* __restrict__ x,
+                                                      const double* __restrict__ sigma,
+                                                      const int64_t* __restrict__ off,
+                                                      int bpc, int shared_t,
+                                                      MomPart* __restrict__ part,
+                                                      const double* __restrict__ scale, Geom g,
+                                                      Moments* __restrict__ mom,
+                                                      double* __restrict__ chi2_out) {
+  __shared__ double red[kNT / 64];
+  __shared__ uint32_t bad_s;
+  const int c = blockIdx.y;
+  const int b = blockIdx.x;
+  const int tid = threadIdx.x;
+  const int64_t a = shared_t ? off[0] : off[c], e = shared_t ? off[1] : off[c + 1];
+  const int64_t xs = shared_t ? (int64_t)c * (e - a) : 0;
+  const int64_t n = e - a;
+  const int64_t chunk = (n + bpc - 1) / bpc;
+  const int64_t lo = a + (int64_t)b * chunk;
+  const int64_t hi = (lo + chunk < e) ? lo + chunk : e;
+  if (tid == 0) bad_s = 0;
+  __syncthreads();
+  double sw = 0.0, swx = 0.0;
+  uint32_t bad = 0;
+  for (int64_t i = lo + tid; i < hi; i += kNT) {
+    const double ti = t[i], xi = x[i + xs], si = sigma[i];
+    if (!isfinite(ti) || !isfinite(xi) || !isfinite(si) || !(si > 0.0)) bad |= CF_NONFINITE;
+    if (i > a && !(ti >= t[i - 1])) bad |= CF_UNSORTED;
+    const double w = 1.0 / (si * si);
+    sw += w;
+    swx += w * xi;
+  }
+  if (bad) atomicOr(&bad_s, bad);
+  const double W = block_sum(sw, red);
+  const double WX = block_sum(swx, red);
+  const double mean = (W > 0.0) ? WX / W : 0.0;
+  double sc = 0.0;
+  for (int64_t i = lo + tid; i < hi; i += kNT) {
+    const double si = sigma[i];
+    const double y = x[i + xs] - mean;
+    sc += y * y / (si * si);
+  }
+  const double M2 = block_sum(sc, red);
+  if constexpr (ONE) {
+    if (tid == 0) {
+      double W1 = 0.0, mean1 = 0.0, M21 = 0.0;
+      mom_combine(W1, mean1, M21, W, mean, M2);
+      moments_write(t, off, c, shared_t, scale, g, W1, mean1, M21, bad_s, mom, chi2_out);
+    }
+  } else if (tid == 0) {
+    MomPart pp;
+    pp.W = W;
+    pp.mean = mean;
+    pp.M2 = M2;
+    pp.bad = bad_s;
+    pp.pad = 0;
+    part[(int64_t)c * bpc + b] = pp;
+  }
+}
+
+// Phase 2: one wave per curve.  Lane j combines chunks j, j + 64, ... in
+// order, then the 64 lane summaries are combined by a fixed pairwise tree
+// (deterministic); lane 0 writes the curve's Moments and chi2_0.
+__global__ __launch_bounds__(64) void k_moments_fin(const double* __restrict__ t,
+                                                    const int64_t* __restrict__ off,
+                                                    int n_curves, int bpc, int shared_t,
+                                                    const double* __restrict__ scale,
+                                                    const MomPart* __restrict__ part, Geom g,
+                                                    Moments* __restrict__ mom,
+                                                    double* __restrict__ chi2_out) {
+  const int c = blockIdx.x;
+  const int lane = threadIdx.x;
+  double W = 0.0, mean = 0.0, M2 = 0.0;
+  uint32_t fl = 0;
+  for (int b = lane; b < bpc; b += 64) {
+    const MomPart pp = part[(int64_t)c * bpc + b];
+    fl |= pp.bad;
+    mom_combine(W, mean, M2, pp.W, pp.mean, pp.M2);
+  }
+  for (int o = 1; o < 64; o <<= 1) {
+    const double W2 = __shfl_down(W, o), mean2 = __shfl_down(mean, o), M22 = __shfl_down(M2, o);
+    const uint32_t f2 = (uint32_t)__shfl_down((int)fl, o);
+    if ((lane & (2 * o - 1)) == 0) {
+      mom_combine(W, mean, M2, W2, mean2, M22);
+      fl |= f2;
+    }
+  }
+  if (lane != 0) return;
+  moments_write(t, off, c, shared_t, scale, g, W, mean, M2, fl, mom, chi2_out);
 }
 
 __global__ __launch_bounds__(kNT) void k_tile_bounds(const double* __restrict__ t,
@@ -258,8 +280,13 @@ hipError_t launch_moments(const double* t, const double* x, const double* sigma,
                           const int64_t* offsets, int n_curves, int bpc, const Geom& g,
                           MomPart* part, Moments* mom, double* chi2_0, hipStream_t st,
                           bool shared_t, const double* scale) {
-  hipLaunchKernelGGL(k_moments_part, dim3(bpc, n_curves), dim3(kNT), 0, st, t, x, sigma,
-                     offsets, bpc, shared_t ? 1 : 0, part);
+  if (bpc == 1) {
+    hipLaunchKernelGGL(k_moments_part<true>, dim3(1, n_curves), dim3(kNT), 0, st, t, x, sigma,
+                       offsets, bpc, shared_t ? 1 : 0, part, scale, g, mom, chi2_0);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(k_moments_part<false>, dim3(bpc, n_curves), dim3(kNT), 0, st, t, x, sigma,
+                     offsets, bpc, shared_t ? 1 : 0, part, scale, g, mom, chi2_0);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_moments_fin, dim3(n_curves), dim3(64), 0, st, t, offsets, n_curves, bpc,
