@@ -415,9 +415,10 @@ bool use_overlap(const fchi2_plan_s* pl, int n) {
 // the main stream runs wave i's FFT passes and what follows them (`tail`,
 // made per wave from (c0, nw, spectra): the solve, or the solve with the
 // candidate selection).  Wave i spreads into grid A buffer i % 2 (halves of
-// the grid A region) with table i % 2 (halves of the table region); the side
-// stream waits for the first pass that last read that buffer (wave i - 2),
-// the main stream for wave i's spreading.  Every kernel is the one-stream
+// the grid A region); the side stream waits for the first pass that last read
+// that buffer (wave i - 2), the main stream for wave i's spreading.  The tile
+// table is written and read on the side stream alone, one wave after another,
+// so every wave takes the whole table region.  Every kernel is the one-stream
 // search's on the same curves, so the results are identical bit for bit.
 // Every piece of side-stream work is waited on by the main stream before the
 // call returns to it, so graph capture joins.
@@ -429,7 +430,7 @@ fchi2_status_t enqueue_waves_overlap(fchi2_plan_s* pl, int cbeg, int cend, const
   const bool keep = pl->desc.flags & FCHI2_KEEP_FOR_BACKWARD;
   const size_t zc_curve = (size_t)pl->g.P * 2 * pl->g.n_freq * pl->elem;
   const size_t grid_curve = (size_t)pl->g.P * (size_t)pl->g.L * pl->elem;
-  const size_t tb_half = align256(tile_bounds_bytes(pl->g, kFusedTbLog, pl->wave));
+  int32_t* tb = (int32_t*)(ws + pl->off_tb);
   hipStream_t sd = pl->side;
   hipError_t e = hipEventRecord(pl->ev_start, st);  // moments are done before any spreading
   if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
@@ -440,7 +441,6 @@ fchi2_status_t enqueue_waves_overlap(fchi2_plan_s* pl, int cbeg, int cend, const
     const int nw = (cend - c0) < pl->wave ? (cend - c0) : pl->wave;
     const int b = i & 1;
     char* gA = ws + pl->off_gA + (size_t)b * grid_curve * pl->wave;
-    int32_t* tb = (int32_t*)(ws + pl->off_tb + (size_t)b * tb_half);
     void* gB = ws + pl->off_gB;
     void* zc = ws + pl->off_zc + (keep ? (size_t)c0 * zc_curve : 0);
     if (i >= 2 && (e = hipStreamWaitEvent(sd, pl->ev_first[b], 0)) != hipSuccess)
@@ -1022,8 +1022,8 @@ fchi2_status_t fchi2_plan(const fchi2_plan_desc_t* desc, void* stream, fchi2_pla
   pl->off_part = off;
   off = align256(off + sizeof(MomPart) * (size_t)d.n_curves * pl->mom_bpc);
   pl->off_tb = off;
-  // Sized for the finest table: the fused first pass's tiles of 2^kFusedTbLog
-  // cells (the spreading kernel's tiles are 2^10 cells or more).
+  // Sized for the finest table of a whole wave: 2^kFusedTbLog cells, the tiles
+  // of the fused first pass and the smallest strips of the spreading.
   off = align256(off + tile_bounds_bytes(g, kFusedTbLog, pl->wave));
   pl->off_gA = off;
   off = align256(off + grid_curve * pl->wave);
