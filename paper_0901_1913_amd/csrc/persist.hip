@@ -105,8 +105,8 @@ __device__ __forceinline__ void slot_spread(const PersistArgs& a, const Moments&
 template <int H>
 __device__ __forceinline__ void slot_tables(const PersistArgs& a, const Moments& mo, int32_t* tb) {
   for (int m = 1; m <= 2 * a.g.H; ++m)
-    for (int64_t il = opaque_tid(); il <= mo.n; il += kNT)
-      tile_bounds_point(a.t, mo, a.g, 0, m, il, kSlotLS, a.ntb, tb);
+    for (int64_t b = 0; b <= mo.n; b += kNT)
+      tile_bounds_point(a.t, mo, a.g, 0, m, b + opaque_tid(), kSlotLS, a.ntb, tb);
 }
 
 template <int H>

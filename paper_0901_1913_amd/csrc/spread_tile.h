@@ -30,32 +30,50 @@ __device__ __forceinline__ int64_t tile_limit_of(const Moments& mo, const Geom& 
 }
 
 // The table entries owned by point il (0..n; n: past the last point) of
-// harmonic m for the curve mo in table slot cw.
+// harmonic m for the curve mo in table slot cw.  Every lane of a wave calls it.
+//
+// A lane stores the entries of its own point one after another; an observing
+// gap leaves one point most of a grid's entries, so an interval of more than
+// kOwn is stored by the whole wave, a run of 64 at a time.  Table and spreading
+// with a third of the span empty, one lane storing the gap and the wave: 1e5
+// points on 2^22 bins, H = 5, 1118 and 167 us (without the gap 167); 300 points on 2^24
+// bins, H = 3, 4575 and 347 (300).  kOwn of 4, 8, 32 and 64 measure the same.
 __device__ __forceinline__ void tile_bounds_point(const double* __restrict__ t,
                                                   const Moments& mo, const Geom& g, int cw,
                                                   int m, int64_t il, int log_tile, int ntb,
                                                   int32_t* __restrict__ tb) {
-  if (il > mo.n) return;
+  constexpr int kOwn = 16;
   const double Ld = (double)g.L, coff = (double)g.c_off;
   const double B = (double)((int64_t)1 << log_tile);
   const double shift = (double)(g.w / 2 + 2);
-  int64_t t_min, t_max;
-  if (il == 0) {
-    t_min = 0;
-  } else {
-    const double lo = cell_at(t[mo.start + il - 1], mo.T0, g.df, m, Ld, coff, g.w == 1);
-    t_min = (int64_t)floor((lo + shift) / B) + 1;
+  int64_t t_min = 0, t_max = -1;
+  if (il <= mo.n) {
+    if (il > 0) {
+      const double lo = cell_at(t[mo.start + il - 1], mo.T0, g.df, m, Ld, coff, g.w == 1);
+      t_min = (int64_t)floor((lo + shift) / B) + 1;
+    }
+    if (il == mo.n) {
+      t_max = tile_limit_of(mo, g, m, log_tile);
+    } else {
+      const double hi = cell_at(t[mo.start + il], mo.T0, g.df, m, Ld, coff, g.w == 1);
+      t_max = (int64_t)floor((hi + shift) / B);
+    }
+    if (t_min < 0) t_min = 0;
+    if (t_min > ntb) t_min = ntb;
+    if (t_max > ntb - 1) t_max = ntb - 1;
   }
-  if (il == mo.n) {
-    t_max = tile_limit_of(mo, g, m, log_tile);
-  } else {
-    const double hi = cell_at(t[mo.start + il], mo.T0, g.df, m, Ld, coff, g.w == 1);
-    t_max = (int64_t)floor((hi + shift) / B);
-  }
-  if (t_min < 0) t_min = 0;
-  if (t_max > ntb - 1) t_max = ntb - 1;
+  const int a = (int)t_min, e = (int)t_max;
   int32_t* row = tb + ((int64_t)cw * (2 * g.H) + (m - 1)) * ntb;
-  for (int64_t q = t_min; q <= t_max; ++q) row[q] = (int32_t)il;
+  const bool own = e - a < kOwn;
+  if (own)
+    for (int q = a; q <= e; ++q) row[q] = (int32_t)il;
+  const int lane = (int)(threadIdx.x & 63);
+  for (uint64_t left = __ballot(!own); left; left &= left - 1) {
+    const int src = __ffsll((unsigned long long)left) - 1;
+    const int a1 = __builtin_amdgcn_readlane(a, src), e1 = __builtin_amdgcn_readlane(e, src);
+    const int v = __builtin_amdgcn_readlane((int)il, src);
+    for (int q = a1 + lane; q <= e1; q += 64) row[q] = v;
+  }
 }
 
 // The spreading of one wave: four groups of 16 lanes, each summing one
