@@ -158,7 +158,7 @@ struct fchi2_plan_s {
   double eps_piv = 0.0;
   int wave = 1;
   int wave_max = 1;        // the workspace is sized for this many curves
-  int64_t max_n = 0;
+  int64_t max_n = 0, mean_n = 0;  // points of the longest and of the mean curve
   int64_t n_total = 0;
   // plan-owned device tables
   int64_t* d_off = nullptr;
@@ -448,7 +448,7 @@ fchi2_status_t enqueue_waves_overlap(fchi2_plan_s* pl, int cbeg, int cend, const
     if ((e = prof_mark(pl, FCHI2_PROF_SPREAD, sd)) != hipSuccess)
       return hip_fail(e, "profiling event");
     e = launch_spread(pl->fp64, t, x, sigma, mom, pl->g, c0, nw, pl->max_n, tb,
-                      spread_table_log(pl->g, nw, pl->max_n), gA, sd);
+                      spread_table_log(pl->g, nw, pl->max_n, pl->mean_n), gA, sd);
     if (e != hipSuccess) return hip_fail(e, "spread");
     if ((e = prof_mark(pl, -1, sd)) != hipSuccess) return hip_fail(e, "profiling event");
     if ((e = hipEventRecord(pl->ev_spread[b], sd)) != hipSuccess)
@@ -508,7 +508,7 @@ fchi2_status_t enqueue_search(fchi2_plan_s* pl, int cbeg, int cend, const double
     PROF_BEGIN(FCHI2_PROF_SPREAD);
     if (!use_fused(pl))
       e = launch_spread(pl->fp64, t, x, sigma, mom, pl->g, c0, nw, pl->max_n, tb,
-                        spread_table_log(pl->g, nw, pl->max_n), gA, st);
+                        spread_table_log(pl->g, nw, pl->max_n, pl->mean_n), gA, st);
     else
       e = launch_tile_bounds(t, mom, pl->g, c0, nw, pl->max_n, tb, kFusedTbLog, st);
     if (e != hipSuccess) return hip_fail(e, "spread");
@@ -577,7 +577,7 @@ fchi2_status_t enqueue_search_top(fchi2_plan_s* pl, const double* t, const doubl
     PROF_BEGIN(FCHI2_PROF_SPREAD);
     if (!use_fused(pl))
       e = launch_spread(pl->fp64, t, x, sigma, mom, pl->g, c0, nw, pl->max_n, tb,
-                        spread_table_log(pl->g, nw, pl->max_n), gA, st);
+                        spread_table_log(pl->g, nw, pl->max_n, pl->mean_n), gA, st);
     else
       e = launch_tile_bounds(t, mom, pl->g, c0, nw, pl->max_n, tb, kFusedTbLog, st);
     if (e != hipSuccess) return hip_fail(e, "spread");
@@ -627,7 +627,7 @@ MultiLayout multi_layout(const fchi2_plan_s* pl, int S) {
   size_t cap = ((size_t)8 << 30) / (2 * grid_src);
   if (cap < 1) cap = 1;
   m.wave = (int)(cap < (size_t)S ? cap : (size_t)S);
-  m.ls = spread_table_log(m.gp, m.wave, pl->max_n);
+  m.ls = spread_table_log(m.gp, m.wave, pl->max_n, pl->mean_n);
   const size_t pairs = std::max<size_t>((size_t)pl->g.H, (size_t)m.wave * pd);
   size_t off = 0;
   m.off_mt = off;
@@ -1015,6 +1015,7 @@ fchi2_status_t fchi2_plan(const fchi2_plan_desc_t* desc, void* stream, fchi2_pla
     max_n = n > max_n ? n : max_n;
   }
   pl->max_n = max_n;
+  pl->mean_n = pl->n_total / d.n_curves;
   pl->mom_bpc = (int)std::min<int64_t>(256, std::max<int64_t>(1, (max_n + 1023) / 1024));
   size_t off = 0;
   pl->off_mom = off;

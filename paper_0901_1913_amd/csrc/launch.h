@@ -38,12 +38,12 @@ hipError_t launch_moments(const double* t, const double* x, const double* sigma,
 
 // Spread w and w*(x - xbar) of each curve of the wave onto its P packed grids.
 // tb: tile -> point-range table, tile_bounds_bytes(g, ls, n_curves), with
-// ls = spread_table_log(g, n_curves, max_n).
+// ls = spread_table_log(g, n_curves, max_n, mean_n).
 hipError_t launch_spread(bool fp64, const double* t, const double* x, const double* sigma,
                          const Moments* mom, const Geom& g, int curve0, int n_curves,
                          int64_t max_n, int32_t* tb, int ls, void* grid, hipStream_t st,
                          bool share_tb = false);
-int spread_table_log(const Geom& g, int n_curves, int64_t max_n);
+int spread_table_log(const Geom& g, int n_curves, int64_t max_n, int64_t mean_n);
 size_t tile_bounds_bytes(const Geom& g, int log_tile, int n_curves);
 // The tile table alone (tiles of 2^log_tile cells): the fused first FFT pass
 // reads it to find each row segment's points.

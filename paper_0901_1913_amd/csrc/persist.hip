@@ -31,7 +31,7 @@ constexpr size_t cmax(T a, T b) {
 }
 
 constexpr int kSlotLS = kStripLogMax;  // strips of the spreading
-using SlotSpread = SpreadSmem<kSlotLS, false>;
+using SlotSpread = SpreadSmem<kSlotLS, false, false>;
 
 // LDS of the largest stage: FFT tiles of 4096 FP32 elements (N = 2^5..2^9
 // rows; the middle pass's hold the most) and the spreading of four waves.

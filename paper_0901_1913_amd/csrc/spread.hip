@@ -228,7 +228,7 @@ __global__ __launch_bounds__(kNT) void k_tile_bounds(const double* __restrict__ 
 // Lane p counts pair p's waves, one round of arithmetic instead of one a pair:
 // with short strips a wave's start is most of its time (150 curves of 16 points
 // on 2^10 bins: spreading 38 against 30 us).
-template <typename S, int LS, bool BAND>
+template <typename S, int LS, bool BAND, bool DENSE>
 __global__ __launch_bounds__(kNT) void k_spread(const double* __restrict__ t,
                                                 const double* __restrict__ x,
                                                 const double* __restrict__ sigma,
@@ -236,8 +236,8 @@ __global__ __launch_bounds__(kNT) void k_spread(const double* __restrict__ t,
                                                 int curve0, const int32_t* __restrict__ tb,
                                                 int ntb, int share_tb,
                                                 cplx<S>* __restrict__ grid) {
-  constexpr int kWaveCells = SpreadSmem<LS, BAND>::kCells;
-  __shared__ SpreadSmem<LS, BAND> sh[kNT / 64];
+  constexpr int kWaveCells = SpreadSmem<LS, BAND, DENSE>::kCells;
+  __shared__ SpreadSmem<LS, BAND, DENSE> sh[kNT / 64];
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
   const int cw = blockIdx.y;
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(kNT) void k_spread(const double* __restrict__ t,
   for (int p = 0; p < g.P; ++p) {
     const int n = __builtin_amdgcn_readlane(count, p);
     for (; item < n; item += step)
-      spread_strips<S, LS, BAND>(
+      spread_strips<S, LS, BAND, DENSE>(
           t, x, sigma, mo, g, rows, ntb, p, item * spread_strips_per_wave(BAND),
           grid + ((int64_t)cw * g.P + p) * g.L + (int64_t)item * kWaveCells, sh[wave], lane);
     item -= n;
@@ -319,24 +319,31 @@ hipError_t launch_spread(bool fp64, const double* t, const double* x, const doub
   const int64_t blocks = n_curves < 32 ? 4096 : 16384;
   const int64_t per = std::max<int64_t>(8, blocks / std::max(n_curves, 1));
   dim3 gr((unsigned)std::min(most, per), (unsigned)n_curves);
-  auto launch = [&](auto elem, auto strip, auto band) -> void {
+  auto launch = [&](auto elem, auto strip, auto band, auto dense) -> void {
     using S = decltype(elem);
     constexpr int LS = decltype(strip)::value;
-    constexpr bool BD = decltype(band)::value;
-    hipLaunchKernelGGL((k_spread<S, LS, BD>), gr, dim3(kNT), 0, st, t, x, sigma, mom, g, curve0,
-                       tb, ntb, share_tb ? 1 : 0, (cplx<S>*)grid);
+    constexpr bool BD = decltype(band)::value, DN = decltype(dense)::value;
+    hipLaunchKernelGGL((k_spread<S, LS, BD, DN>), gr, dim3(kNT), 0, st, t, x, sigma, mom, g,
+                       curve0, tb, ntb, share_tb ? 1 : 0, (cplx<S>*)grid);
   };
-  auto by_band = [&](auto elem, auto strip) {
-    if (g.band)
-      launch(elem, strip, std::true_type{});
-    else
-      launch(elem, strip, std::false_type{});
-  };
+  // Dense strips by cells: built into strips of 32 cells, and left out where even
+  // a full grid has less than a point in 128 cells (six waves per SIMD instead of
+  // five: 60 curves of 32 points on 2^12 bins 34 against 38 us).
+  const std::integral_constant<int, kStripLogMin> small{};
+  const std::integral_constant<int, kStripLogMax> large{};
+  const std::true_type yes{};
+  const std::false_type no{};
   auto by_strip = [&](auto elem) {
-    if (ls == kStripLogMin)
-      by_band(elem, std::integral_constant<int, kStripLogMin>{});
+    if (g.band && ls == kStripLogMin)
+      launch(elem, small, yes, no);
+    else if (g.band)
+      launch(elem, large, yes, no);
+    else if (ls == kStripLogMax)
+      launch(elem, large, no, no);
+    else if (max_n * 128 < g.L)
+      launch(elem, small, no, no);
     else
-      by_band(elem, std::integral_constant<int, kStripLogMax>{});
+      launch(elem, small, no, yes);
   };
   if (fp64)
     by_strip(double{});
@@ -366,10 +373,16 @@ hipError_t launch_tile_bounds(const double* t, const Moments* mom, const Geom& g
 // 20 curves of 20480 points, 2^15 bins: 351, 293 and 288 against 647, 344 and 263).
 // Where most strips of 128 are empty there is no sequence to shorten, only empty
 // waves to save (140 points, H = 1, 2^18 bins, the whole search: 53 against 41 us).
-int spread_table_log(const Geom& g, int n_curves, int64_t max_n) {
+// Where strips of 128 hold eight points or more on the mean curve, strips of 32
+// at any size, since they are spread by cells (400 curves, H = 4, 2^12 bins, the
+// harmonics over 7, 20 and 70 % of the grid: 1280 points 540, 373 and 293 us with
+// strips of 128, 225, 212 and 329 with 32; 640 points 301, 201 and 168 against
+// 128, 157 and 237, and on full grids, the more usual, that is too much).
+int spread_table_log(const Geom& g, int n_curves, int64_t max_n, int64_t mean_n) {
   const int64_t waves = (g.L >> 9) * g.P * n_curves;
   const bool dense = max_n * 128 >= 4 * g.L, sparse = max_n * 512 < g.L;
-  return waves < (dense ? 65536 : sparse ? 0 : 20000) ? kStripLogMin : kStripLogMax;
+  const bool all_dense = mean_n * 128 >= 8 * g.L;
+  return all_dense || waves < (dense ? 65536 : sparse ? 0 : 20000) ? kStripLogMin : kStripLogMax;
 }
 
 size_t tile_bounds_bytes(const Geom& g, int log_tile, int n_curves) {

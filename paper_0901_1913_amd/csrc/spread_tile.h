@@ -3,6 +3,7 @@
 #pragma once
 
 #include <cmath>
+#include <type_traits>
 
 #include "fchi2_internal.h"
 #include "es_kernel.h"
@@ -84,11 +85,27 @@ __device__ __forceinline__ void tile_bounds_point(const double* __restrict__ t,
 constexpr int kStripLogMax = 7, kStripLogMin = 5;
 constexpr int spread_strips_per_wave(bool band) { return band ? 4 : 2; }
 
-// The cells of one wave's strips, in FP64 until they are written.
-template <int LS, bool BAND>
-struct SpreadSmem {
+// The points of one component of a dense wave, up to kCellPoints at a time: the
+// cell coordinate relative to the wave's first cell and the strength, with room
+// for the sentinels that end them.  384 points are 24 KB a workgroup, which
+// leaves the five workgroups per CU that the registers allow (FP64: four); with
+// both components staged at once, at half the points, several long curves on
+// small grids (100 of 5000 points, H = 8, 2^11 bins) took a fifth longer.
+constexpr int kCellPoints = 384, kTapUnroll = 4;
+struct CellPoints {
+  double2 q[kCellPoints + kTapUnroll];
+};
+struct NoPoints {};
+
+// What one wave of the spreading holds: the cells of its strips, in FP64 until
+// they are written, or (DENSE) points.
+template <int LS, bool BAND, bool DENSE>
+union SpreadSmem {
   static constexpr int kCells = spread_strips_per_wave(BAND) << LS;
-  double re[kCells], im[kCells];
+  struct {
+    double re[kCells], im[kCells];
+  } cell;
+  typename std::conditional<DENSE, CellPoints, NoPoints>::type pts;
 };
 
 // Sixteen points of a strip, one per lane of its group: the cell coordinate
@@ -133,6 +150,100 @@ __device__ __forceinline__ PointLane load_point(const double* __restrict__ t,
   return q;
 }
 
+// Whether a wave's two strips are spread with a lane per cell, from the points
+// of each lane's group (n).  Fewer than 48 points: a group's sixteen take them in
+// a round or two.  Many in few cells: every cell sees most points, so a lane's
+// own sequence is as long as a strip's, and two components follow each other
+// (640 points, 2^10 bins, H = 4, 18 points a cell in the first pair: FP32 54 us
+// of spreading against 92 with the strips, FP64 146 against 134).
+template <bool EXACT>
+__device__ __forceinline__ bool cells_pay(int n) {
+  const int re = __builtin_amdgcn_readlane(n, 0) + __builtin_amdgcn_readlane(n, 16);
+  const int im = __builtin_amdgcn_readlane(n, 32) + __builtin_amdgcn_readlane(n, 48);
+  return re + im >= 48 && (re > im ? re : im) <= (EXACT ? 1000 : 1500);
+}
+
+// The wave's two strips (64 cells) of packed grid p from `strip` on, a lane per
+// cell, where the strips hold many points: from points staged in LDS a lane adds
+// to its cell the taps within the kernel's reach, in index order, four at a time
+// (the first found by binary search).  Every tap it evaluates is of use, where a
+// group's sixteen lanes share the ten or fourteen of a point, and a point is
+// loaded once for 64 cells instead of once for every strip of 32 that it reaches.
+// Each cell adds the same terms in the same order as in spread_strips.
+//
+// What bounds it: FP64 arithmetic where many curves fill the device, the longest
+// sequence of taps elsewhere.  Spreading of equal curves, H = 4, in us, by a
+// workgroup per tile of 1024 cells (the form before the strips), by strips alone
+// and with this, the harmonics over 7, 20 and 70 % of the grid:
+//   400 of 640 points, 2^10 bins:  201, 130, 172;  357, 274, 207;  220, 127, 145
+//   150 of 5120 points, 2^13 bins: 568, 434, 411;  570, 493, 502;  404, 249, 339
+//   one of 640 points, 2^10 bins:   72,  38,  37;   92,  58,  24;   54,  23,  16
+template <typename S, int LS>
+__device__ __forceinline__ void spread_cells(const double* __restrict__ t,
+                                             const double* __restrict__ x,
+                                             const double* __restrict__ sigma,
+                                             const Moments& mo, const Geom& g,
+                                             const int32_t* __restrict__ rows, int ntb, int p,
+                                             int strip, cplx<S>* __restrict__ out,
+                                             CellPoints& sh, int lane) {
+  static_assert(2 << LS == 64, "a lane per cell of two strips");
+  static_assert(kCellPoints < 512, "the search's first step");
+  constexpr bool EXACT = sizeof(S) == 8;
+  const double two_over_w = 2.0 / (double)g.w;
+  const double beta = g.beta;
+  const double cl = (double)lane, half = 0.5 * (double)g.w;
+  const int nstrip = (int)(g.L >> LS);
+  double acc[2];
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the points take the cells' place
+  // one body for both components: unrolled, its registers cost waves
+#pragma unroll 1
+  for (int c = 0; c < 2; ++c) {
+    const int m = g.comp_m[p][c], kind = g.comp_kind[p][c];
+    const int32_t* row = rows + (int64_t)(m - 1) * ntb;
+    const int lim = m ? (int)tile_limit_of(mo, g, m, LS) : 0;
+    double a = 0.0;
+    for (int lap = 0; lap < g.laps; ++lap) {
+      const int ut = strip + lap * nstrip;
+      if (ut + 2 > lim) break;  // no point reaches this far
+      const double base = (double)((int64_t)ut << LS);
+      int lo = __builtin_amdgcn_readfirstlane(row[ut]);
+      const int hi = __builtin_amdgcn_readfirstlane(row[ut + 3 <= lim ? ut + 3 : lim]);
+      while (lo < hi) {
+        const int n = hi - lo < kCellPoints ? hi - lo : kCellPoints;
+        for (int i = lane; i < n; i += 64) {
+          const PointLane pt =
+              load_point<false>(t, x, sigma, mo, g, m, kind, mo.start + lo + i, base);
+          sh.q[i] = make_double2(pt.rel, pt.re);
+        }
+        if (lane < kTapUnroll) sh.q[n + lane] = make_double2(1e300, 0.0);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const double2* q = sh.q;
+        int k = 0;
+#pragma unroll
+        for (int step = 256; step > 0; step >>= 1)
+          if (k + step <= n && q[k + step - 1].x < cl - half) k += step;
+        while (q[k].x <= cl + half) {
+          double phi[kTapUnroll], v[kTapUnroll];
+#pragma unroll
+          for (int u = 0; u < kTapUnroll; ++u) {
+            phi[u] = es_kernel<EXACT>((cl - q[k + u].x) * two_over_w, beta);
+            v[u] = q[k + u].y;
+          }
+#pragma unroll
+          for (int u = 0; u < kTapUnroll; ++u) a = fma(phi[u], v[u], a);
+          k = k + kTapUnroll < n ? k + kTapUnroll : n;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        lo += n;
+      }
+    }
+    (c ? acc[1] : acc[0]) = a;
+  }
+  out[lane] = cmk<S>((S)acc[0], (S)acc[1]);
+}
+
 // The wave's strips from `strip` on, of packed grid p of the curve mo (its table
 // rows at `rows`, ntb entries per harmonic), written to out.  One wave calls
 // it; sh is the wave's own.
@@ -152,17 +263,18 @@ __device__ __forceinline__ PointLane load_point(const double* __restrict__ t,
 // broadcasts, a DPP row being a group, with no LDS permute on the chain of one
 // point's tap (150 curves of 5120 points, H = 4, 2^13 bins: 571 us with the
 // permutes, 496 now; 20 curves of 1280 points on 2^11 bins: 92 and 75).
-template <typename S, int LS, bool BAND>
+template <typename S, int LS, bool BAND, bool DENSE = false>
 __device__ __forceinline__ void spread_strips(const double* __restrict__ t,
                                               const double* __restrict__ x,
                                               const double* __restrict__ sigma,
                                               const Moments& mo, const Geom& g,
                                               const int32_t* __restrict__ rows, int ntb, int p,
                                               int strip, cplx<S>* __restrict__ out,
-                                              SpreadSmem<LS, BAND>& sh, int lane) {
+                                              SpreadSmem<LS, BAND, DENSE>& smem, int lane) {
   constexpr bool EXACT = sizeof(S) == 8;
   constexpr int kStrip = 1 << LS;
-  constexpr int kWaveCells = SpreadSmem<LS, BAND>::kCells;
+  constexpr int kWaveCells = SpreadSmem<LS, BAND, DENSE>::kCells;
+  auto& sh = smem.cell;
   const int grp = lane >> 4, r = lane & 15;
   const double two_over_w = 2.0 / (double)g.w;
   const double beta = g.beta;
@@ -193,6 +305,12 @@ __device__ __forceinline__ void spread_strips(const double* __restrict__ t,
     if (any) {
       lo = mo.start + row[ut];
       hi = mo.start + row[ut + 2];
+    }
+    if constexpr (DENSE) {
+      if (lap == 0 && cells_pay<EXACT>((int)(hi - lo))) {
+        spread_cells<S, LS>(t, x, sigma, mo, g, rows, ntb, p, strip, out, smem.pts, lane);
+        return;
+      }
     }
     const double base = (double)((int64_t)ut << LS);
     int cur = -1;  // the lane's cell in hand

@@ -87,7 +87,7 @@ namespace fchi2 {
 size_t tile_bounds_bytes(const Geom& g, int log_tile, int n) {
   return sizeof(int32_t) * (size_t)n * (size_t)(2 * g.H) * (size_t)((g.L >> log_tile) * g.laps + 2);
 }
-int spread_table_log(const Geom&, int, int64_t) { return g_ls; }
+int spread_table_log(const Geom&, int, int64_t, int64_t) { return g_ls; }
 int persist_table_log() { return 7; }
 hipError_t persist_occupancy(int, int* n) {
   *n = 0;  // staged searches only
