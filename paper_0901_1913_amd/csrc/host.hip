@@ -385,7 +385,6 @@ fchi2_status_t enqueue_persistent(fchi2_plan_s* pl, int cbeg, int cend, const do
   a.D = (const cplx<double>*)pl->d_D;
   a.curve_base = cbeg;
   a.n_curves = cend - cbeg;
-  a.ntb = (int)((pl->g.L >> persist_table_log()) * pl->g.laps) + 2;
   a.slots = ws + pl->off_gA;
   a.slot_bytes = pl->slot_bytes;
   a.off_gB = pl->slot_gB;

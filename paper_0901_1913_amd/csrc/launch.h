@@ -81,7 +81,6 @@ struct PersistArgs {
   const cplx<double>* D;
   int curve_base;
   int n_curves;
-  int ntb;
   char* slots;
   size_t slot_bytes, off_gB, off_zc, off_tb;
   int* next;
@@ -89,7 +88,7 @@ struct PersistArgs {
   float* out;
   uint8_t* flags;
 };
-int persist_table_log();  // granularity of a slot's tile table
+int persist_table_log();  // finest granularity of a slot's tile table
 size_t persist_smem_bytes();
 hipError_t persist_occupancy(int H, int* blocks_per_cu);
 hipError_t launch_persistent(const PersistArgs& a, int n_slots, hipStream_t st);

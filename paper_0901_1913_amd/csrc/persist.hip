@@ -30,8 +30,9 @@ constexpr size_t cmax(T a, T b) {
   return a > b ? a : b;
 }
 
-constexpr int kSlotLS = kStripLogMax;  // strips of the spreading
-using SlotSpread = SpreadSmem<kSlotLS, false, false>;
+// Strips of the spreading: 128 cells, and 32 for dense curves.
+using SlotSpread = SpreadSmem<kStripLogMax, false, false>;
+using SlotDense = SpreadSmem<kStripLogMin, false, true>;
 
 // LDS of the largest stage: FFT tiles of 4096 FP32 elements (N = 2^5..2^9
 // rows; the middle pass's hold the most) and the spreading of four waves.
@@ -39,7 +40,7 @@ constexpr size_t kSmemBytes =
     cmax(cmax(cmax(sizeof(FftSmem<float, 5, 7, TILE_MID>), sizeof(FftSmem<float, 6, 6, TILE_MID>)),
               cmax(sizeof(FftSmem<float, 7, 5, TILE_MID>), sizeof(FftSmem<float, 8, 4, TILE_MID>))),
          cmax(sizeof(FftSmem<float, 9, 3, TILE_MID>),
-              sizeof(SlotSpread[kNT / 64])));
+              cmax(sizeof(SlotSpread[kNT / 64]), sizeof(SlotDense[kNT / 64]))));
 
 template <typename T>
 __device__ __forceinline__ T& smem_as(unsigned char* p) {
@@ -91,22 +92,43 @@ __device__ __forceinline__ void slot_pass(const PersistArgs& a, const FftPassArg
     slot_tiles<LOGN, TILE_LAST>(a, fa, in, out, p, c, zpair, smem);
 }
 
+// A curve whose points are many a cell (forty in 128 cells of its highest
+// harmonic) takes strips of 32 cells, spread by cells where they are dense; one
+// workgroup runs all its strips, so elsewhere fewer and longer ones are faster.
+// 800 curves, H = 3, the whole search by workgroup tiles (before the strips), by
+// strips of 128 alone and now: 600 points on 2^11 bins, the harmonics over 7 % of
+// the grid, 646, 1140 and 535 us; 3000 points, over 170 %, 28 in 128 cells, 1992
+// and 1746 with strips of 128, 2103 with 32.
+__device__ __forceinline__ bool slot_dense(const Moments& mo, const Geom& g) {
+  const double cells = (double)(2 * g.H) * (mo.span * g.df) * (double)g.L;
+  return 128.0 * (double)mo.n >= 40.0 * cells;
+}
+
+template <int LS>
+__device__ __forceinline__ int slot_entries(const Geom& g) {
+  return (int)((g.L >> LS) * g.laps) + 2;
+}
+
+template <int LS, bool DENSE>
 __device__ __forceinline__ void slot_spread(const PersistArgs& a, const Moments& mo, int p,
                                             const int32_t* tb, cplx<float>* gA,
                                             unsigned char* smem) {
-  const int n = (int)(pair_extent(mo, a.g, p) / SlotSpread::kCells);
+  using Smem = SpreadSmem<LS, false, DENSE>;
+  const int n = (int)(pair_extent(mo, a.g, p) / Smem::kCells);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  SlotSpread& sh = smem_as<SlotSpread[kNT / 64]>(smem)[wave];
+  Smem& sh = smem_as<Smem[kNT / 64]>(smem)[wave];
   for (int item = wave; item < n; item += kNT / 64)
-    spread_strips<float, kSlotLS, false>(a.t, a.x, a.sigma, mo, a.g, tb, a.ntb, p, item * spread_strips_per_wave(false),
-                                gA + (int64_t)item * SlotSpread::kCells, sh, opaque_tid() & 63);
+    spread_strips<float, LS, false, DENSE>(
+        a.t, a.x, a.sigma, mo, a.g, tb, slot_entries<LS>(a.g), p,
+        item * spread_strips_per_wave(false), gA + (int64_t)item * Smem::kCells, sh,
+        opaque_tid() & 63);
 }
 
-template <int H>
+template <int LS>
 __device__ __forceinline__ void slot_tables(const PersistArgs& a, const Moments& mo, int32_t* tb) {
   for (int m = 1; m <= 2 * a.g.H; ++m)
     for (int64_t b = 0; b <= mo.n; b += kNT)
-      tile_bounds_point(a.t, mo, a.g, 0, m, b + opaque_tid(), kSlotLS, a.ntb, tb);
+      tile_bounds_point(a.t, mo, a.g, 0, m, b + opaque_tid(), LS, slot_entries<LS>(a.g), tb);
 }
 
 template <int H>
@@ -151,10 +173,17 @@ __global__ __launch_bounds__(kNT, persist_waves<H>()) void k_search_persistent(P
     const int c = a.curve_base + cq;
     const Moments mo = a.mom[c];
     if (!(mo.flags & kCurveFatal)) {
-      slot_tables<H>(a, mo, tb);
+      const bool dense = slot_dense(mo, g);
+      if (dense)
+        slot_tables<kStripLogMin>(a, mo, tb);
+      else
+        slot_tables<kStripLogMax>(a, mo, tb);
       __syncthreads();
       for (int p = 0; p < g.P; ++p) {
-        slot_spread(a, mo, p, tb, gA, smem);
+        if (dense)
+          slot_spread<kStripLogMin, true>(a, mo, p, tb, gA, smem);
+        else
+          slot_spread<kStripLogMax, false>(a, mo, p, tb, gA, smem);
         __syncthreads();
         for (int q = a.fa[1].np; q >= 1; --q) {
           const FftPassArgs& fa = a.fa[q];
@@ -181,7 +210,7 @@ __global__ void k_queue_reset(int* next) { *next = 0; }
 
 }  // namespace
 
-int persist_table_log() { return kSlotLS; }
+int persist_table_log() { return kStripLogMin; }
 
 size_t persist_smem_bytes() { return kSmemBytes; }
 

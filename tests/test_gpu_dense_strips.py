@@ -3,7 +3,8 @@ harmonic 1 around every count at which that is decided (48 points of both
 components, 1000 or 1500 of one) and at which points are staged anew (384), with
 points on cells, on cell edges and in a single cell, and the other harmonics'
 blocks stretched over more.  The cells, hence all results, are those of the
-spreading fused into the first FFT pass, bit for bit, and agree with the oracle."""
+spreading fused into the first FFT pass and of the persistent search, bit for bit,
+and agree with the oracle."""
 import numpy as np
 import pytest
 
@@ -56,16 +57,20 @@ def test_dense_strips_identical_to_fused_and_match_the_oracle(H, width, wrap, pr
     off = np.concatenate([[0], np.cumsum([len(c[0]) for c in per])])
     dev = [torch.from_numpy(np.concatenate([c[i] for c in per])).cuda() for i in range(3)]
     outs = []
-    for fused in (False, True):
-        note(f"dense strips H {H} w {width} wrap {wrap} {precision} fused {fused}")
-        plan = F.Plan(off, f_max, H, NF, precision=precision, kernel_width=width, fused_spread=fused)
-        assert bool(plan.info()["fused_spread"]) == fused
+    for mode in ("staged", "fused_spread", "persistent"):
+        if mode == "persistent" and precision == "fp64":
+            continue  # mixed plans only
+        note(f"dense strips H {H} w {width} wrap {wrap} {precision} {mode}")
+        kw = {} if mode == "staged" else {mode: True}
+        plan = F.Plan(off, f_max, H, NF, precision=precision, kernel_width=width, **kw)
+        assert all(plan.info()[k] for k in kw)
         d, c0, fl = plan.search(*dev)
         torch.cuda.synchronize()
         outs.append([v.cpu() for v in (d, c0, fl)])
         plan.close()
-    for a, b in zip(*outs):
-        assert same_bits(a, b)
+    for other in outs[1:]:
+        for a, b in zip(outs[0], other):
+            assert same_bits(a, b)
     if width in (0, 16):
         bins = sample_bins(NF, 40, 9)
         fr = bins * (f_max / NF)
