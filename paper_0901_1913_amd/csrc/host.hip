@@ -147,7 +147,7 @@ struct fchi2_plan_s {
   // Overlap of the next wave's spreading with this wave's FFT passes and
   // solve: a second stream (default priority) and the events that order the
   // two; used for waves of at most wave_max / 2 curves, whose two spread
-  // grids and tile tables fit in the one-wave buffers.
+  // grids fit in the one-wave grid buffer.
   hipStream_t side = nullptr;
   hipEvent_t ev_start = nullptr, ev_spread[2] = {nullptr, nullptr},
              ev_first[2] = {nullptr, nullptr};
@@ -334,10 +334,10 @@ fchi2_status_t enqueue_fft(fchi2_plan_s* pl, int mode, void* gA, void* gB, void*
 // Whether the forward chain spreads inside the first FFT pass.
 bool use_fused(const fchi2_plan_s* pl) { return pl->fused && pl->fp.np >= 2 && !pl->g.band; }
 
-// Whether the persistent kernel can run split f with spreading tiles of
+// Whether the persistent kernel can run split f with extents rounded to
 // 2^tile cells: mixed precision, H <= 8, no band, no kept spectra, grids of
 // at most 2^20 cells (one workgroup transforms a whole curve), every pass a
-// tile of 2^12 elements of 2^5..2^9 rows, spreading tiles of 2^10 or 2^11.
+// tile of 2^12 elements of 2^5..2^9 rows, extents rounded to 2^10 or 2^11.
 bool persist_ok(const fchi2_plan_s* pl, const FftPlan& f, int tile) {
   if (pl->n_slots < 1 || pl->fp64 || pl->g.band || pl->g.H > kHMax) return false;
   if (pl->g.L > ((int64_t)1 << 20)) return false;
@@ -1046,9 +1046,9 @@ fchi2_status_t fchi2_plan(const fchi2_plan_desc_t* desc, void* stream, fchi2_pla
 
   // Persistent search slots: as many workgroups as fit on the device at once
   // (no more than there are curves), each with one pair's grids, all pairs'
-  // spectra and the tile table (tiles of 2^10 cells), laid out over the wave
-  // buffers (gA, gB, zc), which the persistent search does not otherwise use;
-  // never more slots than fit there.
+  // spectra and the strips' tile table (sized for the finest strips; a curve
+  // picks its own), laid out over the wave buffers (gA, gB, zc), which the
+  // persistent search does not otherwise use; never more slots than fit there.
   if (!pl->fp64 && !g.band && d.H <= kHMax && !keep) {
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
@@ -1728,7 +1728,7 @@ fchi2_status_t fchi2_plan_set_schedule(fchi2_plan_t plan, const int32_t* info, i
   fchi2_plan_s* pl = plan;
   const int np = info[0];
   const int tile = info[5], wave = info[6], fz = info[12], ps = info[13];
-  if (tile < 10 || tile > 13) return fail(FCHI2_ERR_ARG, "spreading tile must be 2^10..2^13");
+  if (tile < 10 || tile > 13) return fail(FCHI2_ERR_ARG, "extent rounding must be 2^10..2^13 cells");
   if (wave < 1 || wave > pl->wave_max)
     return fail(FCHI2_ERR_ARG, "curves per wave must be in 1..%d", pl->wave_max);
   if ((fz != 0 && fz != 1) || (ps != 0 && ps != 1))

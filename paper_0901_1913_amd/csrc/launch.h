@@ -62,7 +62,7 @@ hipError_t launch_pass2_tw(const void* small, int logn, int logL, void* col, voi
                            hipStream_t st);
 
 // Persistent batched search (MIXED plans, H <= 8, FFT splits of 4096-element
-// tiles with 2^5..2^9 rows per pass, spreading tiles of 2^10 or 2^11 cells):
+// tiles with 2^5..2^9 rows per pass, extents rounded to 2^10 or 2^11 cells):
 // one launch of n_slots workgroups takes curves [curve_base, curve_base +
 // n_curves) from the queue counter *next and runs each one's whole chain in
 // its own slot of slot_bytes (gA at 0, gB at off_gB, spectra at off_zc, tile

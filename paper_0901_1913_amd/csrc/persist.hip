@@ -145,8 +145,9 @@ __device__ __forceinline__ void slot_solve(const PersistArgs& a, int c, const cp
   }
 }
 
-// Waves per SIMD the kernel is compiled for: the solve's registers grow with
-// H; up to H = 3 every stage fits 168 registers (three workgroups per CU).
+// Waves per SIMD the kernel is compiled for: the solve's registers grow with H.
+// Up to H = 3 three workgroups per CU: 168 registers, with some 200 bytes a lane
+// spilled by the two sizes of strips.
 template <int H>
 constexpr int persist_waves() {
   return H <= 3 ? 3 : (H <= 5 ? 2 : 1);

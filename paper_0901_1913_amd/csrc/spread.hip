@@ -19,9 +19,9 @@
 // Two real grids are packed per complex grid (real part, imaginary part);
 // each wave owns strips of consecutive cells of one packed grid and sums the
 // kernel contributions of their points tap by tap, every cell in point order
-// (deterministic, no atomics).  The arithmetic is FP64 (for float grids the kernel's exponential is taken to
-// FP32 accuracy, see es_kernel.h); the grid is stored as S (float for mixed
-// plans).
+// (deterministic, no atomics).  The arithmetic is FP64 (for float grids the
+// kernel's exponential is taken to FP32 accuracy, see es_kernel.h); the grid is
+// stored as S (float for mixed plans).
 #include <algorithm>
 #include <cmath>
 #include <type_traits>

@@ -408,7 +408,7 @@ class Plan:
         return (x_out, coef) if want_coef else x_out
 
     def autotune_multi(self, t, sigma, x, scale, stream=None):
-        """Pick the FFT split and spreading tile for search_multi on these data."""
+        """Pick the FFT split and extent rounding for search_multi on these data."""
         torch = _torch()
         f64 = torch.float64
         S = int(x.shape[0])
@@ -581,7 +581,8 @@ class Plan:
         return self.info()
 
     def info(self) -> dict:
-        """The plan's schedule: FFT radices, spreading tile, wave, kernel width."""
+        """The plan's schedule: FFT radices, extent rounding (spread_tile), wave,
+        kernel width."""
         arr = (ctypes.c_int32 * 15)()
         _check(lib().fchi2_plan_info(self._h, arr, 15))
         np_ = int(arr[0])
@@ -593,7 +594,7 @@ class Plan:
 
     def set_schedule(self, schedule: dict) -> dict:
         """Apply a schedule as info() reports it (FFT radices and tiles,
-        spreading tile, curves per wave, fused, persistent) without timing."""
+        extent rounding, curves per wave, fused, persistent) without timing."""
         arr = (ctypes.c_int32 * 15)()
         ln = list(schedule["fft_log_radices"])
         le = list(schedule["fft_log_tiles"])
