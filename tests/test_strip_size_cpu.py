@@ -1,0 +1,25 @@
+"""Host build of the spreading's choice of strip size (csrc/spread.hip,
+spread_table_log): dense launches of any size take strips of 32 cells, spread by
+cells, except band plans, whose strips have no such form; elsewhere the number
+of waves decides."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+SRC = os.path.join(HERE, "host", "strip_size_test.hip")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None and not os.path.exists(HIPCC),
+                    reason="hipcc not available")
+def test_strip_size(tmp_path):
+    exe = str(tmp_path / "strip_size_test")
+    r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-Xclang",
+                        "-target-feature", "-Xclang", "-packed-fp32-ops", SRC, "-o", exe],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    out = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0 and "ALL OK" in out.stdout, out.stdout + out.stderr
