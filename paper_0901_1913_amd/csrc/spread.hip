@@ -334,16 +334,19 @@ hipError_t launch_spread(bool fp64, const double* t, const double* x, const doub
   const std::true_type yes{};
   const std::false_type no{};
   auto by_strip = [&](auto elem) {
-    if (g.band && ls == kStripLogMin)
-      launch(elem, small, yes, no);
-    else if (g.band)
+    const bool dense = max_n * 128 >= g.L;
+    if (ls == kStripLogMax && g.band)
       launch(elem, large, yes, no);
     else if (ls == kStripLogMax)
       launch(elem, large, no, no);
-    else if (max_n * 128 < g.L)
-      launch(elem, small, no, no);
-    else
+    else if (g.band && dense)
+      launch(elem, small, yes, yes);
+    else if (g.band)
+      launch(elem, small, yes, no);
+    else if (dense)
       launch(elem, small, no, yes);
+    else
+      launch(elem, small, no, no);
   };
   if (fp64)
     by_strip(double{});
@@ -377,13 +380,15 @@ hipError_t launch_tile_bounds(const double* t, const Moments* mom, const Geom& g
 // at any size, since they are spread by cells (400 curves, H = 4, 2^12 bins, the
 // harmonics over 7, 20 and 70 % of the grid: 1280 points 540, 373 and 293 us with
 // strips of 128, 225, 212 and 329 with 32; 640 points 301, 201 and 168 against
-// 128, 157 and 237, and on full grids, the more usual, that is too much).  Not
-// for band plans, whose strips are never spread by cells (1e6 points, H = 8, a
-// band of 2^21 bins, the whole search: 2.15 ms with strips of 32, 1.83 with 128).
+// 128, 157 and 237, and on full grids, the more usual, that is too much).  Band plans:
+// sixteen, a wave's 128 cells then holding the 48 points it takes (300 curves of
+// 3000 points, 23 in 128 cells, H = 5, 2^13 bins, over 10, 80 and 170 %: 1717,
+// 1109 and 1147 us against 1157, 990 and 1213; 1e6 points, H = 8, one of eight
+// bands, 2^21 bins: 1880 against 1690).
 int spread_table_log(const Geom& g, int n_curves, int64_t max_n, int64_t mean_n) {
   const int64_t waves = (g.L >> 9) * g.P * n_curves;
   const bool dense = max_n * 128 >= 4 * g.L, sparse = max_n * 512 < g.L;
-  const bool all_dense = !g.band && mean_n * 128 >= 8 * g.L;
+  const bool all_dense = mean_n * 128 >= (g.band ? 16 : 8) * g.L;
   return all_dense || waves < (dense ? 65536 : sparse ? 0 : 20000) ? kStripLogMin : kStripLogMax;
 }
 

@@ -88,12 +88,19 @@ constexpr int spread_strips_per_wave(bool band) { return band ? 4 : 2; }
 // The points of one component of a dense wave, up to kCellPoints at a time: the
 // cell coordinate relative to the wave's first cell and the strength, with room
 // for the sentinels that end them.  384 points are 24 KB a workgroup, which
-// leaves the five workgroups per CU that the registers allow (FP64: four); with
+// leaves the five workgroups per CU that the registers allow (FP64: four; the
+// complex strengths of band plans: 36 KB, four, FP64 three); with
 // both components staged at once, at half the points, several long curves on
 // small grids (100 of 5000 points, H = 8, 2^11 bins) took a fifth longer.
 constexpr int kCellPoints = 384, kTapUnroll = 4;
+template <bool BAND>
 struct CellPoints {
   double2 q[kCellPoints + kTapUnroll];
+};
+template <>
+struct CellPoints<true> {
+  double2 q[kCellPoints + kTapUnroll];
+  double im[kCellPoints + kTapUnroll];
 };
 struct NoPoints {};
 
@@ -105,7 +112,7 @@ union SpreadSmem {
   struct {
     double re[kCells], im[kCells];
   } cell;
-  typename std::conditional<DENSE, CellPoints, NoPoints>::type pts;
+  typename std::conditional<DENSE, CellPoints<BAND>, NoPoints>::type pts;
 };
 
 // Sixteen points of a strip, one per lane of its group: the cell coordinate
@@ -150,25 +157,28 @@ __device__ __forceinline__ PointLane load_point(const double* __restrict__ t,
   return q;
 }
 
-// Whether a wave's two strips are spread with a lane per cell, from the points
-// of each lane's group (n).  Fewer than 48 points: a group's sixteen take them in
-// a round or two.  Many in few cells: every cell sees most points, so a lane's
-// own sequence is as long as a strip's, and two components follow each other
-// (640 points, 2^10 bins, H = 4, 18 points a cell in the first pair: FP32 54 us
-// of spreading against 92 with the strips, FP64 146 against 134).
-template <bool EXACT>
+// Whether a wave's strips are spread with a lane per cell, from the points of each
+// lane's group (n).  Fewer than 48 points: a group's sixteen take them in a round
+// or two.  Many in few cells: every cell sees most points, so a lane's own
+// sequence is as long as a strip's, and the two components (band plans: the two
+// runs of 64 cells) follow each other (640 points, 2^10 bins, H = 4, 18 points a
+// cell in the first pair: FP32 54 us of spreading against 92 with the strips, FP64
+// 146 against 134; 20 bands of 3000 points, 2^11 bins, H = 2, 30 a cell, the whole
+// search by cells throughout 336 against 291 us, FP64 853 against 460).
+template <bool EXACT, bool BAND>
 __device__ __forceinline__ bool cells_pay(int n) {
-  const int re = __builtin_amdgcn_readlane(n, 0) + __builtin_amdgcn_readlane(n, 16);
-  const int im = __builtin_amdgcn_readlane(n, 32) + __builtin_amdgcn_readlane(n, 48);
-  return re + im >= 48 && (re > im ? re : im) <= (EXACT ? 1000 : 1500);
+  const int a = __builtin_amdgcn_readlane(n, 0) + __builtin_amdgcn_readlane(n, 16);
+  const int b = __builtin_amdgcn_readlane(n, 32) + __builtin_amdgcn_readlane(n, 48);
+  if constexpr (BAND) return a + b >= 48 && a + b <= (EXACT ? 2000 : 3000);
+  return a + b >= 48 && (a > b ? a : b) <= (EXACT ? 1000 : 1500);
 }
 
-// The wave's two strips (64 cells) of packed grid p from `strip` on, a lane per
-// cell, where the strips hold many points: from points staged in LDS a lane adds
-// to its cell the taps within the kernel's reach, in index order, four at a time
-// (the first found by binary search).  Every tap it evaluates is of use, where a
-// group's sixteen lanes share the ten or fourteen of a point, and a point is
-// loaded once for 64 cells instead of once for every strip of 32 that it reaches.
+// The wave's strips of packed grid p from `strip` on, a lane per cell (band plans:
+// two, 64 cells apart), where they hold many points: from points staged in LDS a
+// lane adds to its cell the taps within the kernel's reach, in index order, four
+// at a time (the first found by binary search).  Every tap it evaluates is of use,
+// where a group's sixteen lanes share the ten or fourteen of a point, and a point
+// is loaded once for the wave instead of once for every strip of 32 that it reaches.
 // Each cell adds the same terms in the same order as in spread_strips.
 //
 // What bounds it: FP64 arithmetic where many curves fill the device, the longest
@@ -178,70 +188,106 @@ __device__ __forceinline__ bool cells_pay(int n) {
 //   400 of 640 points, 2^10 bins:  201, 130, 172;  357, 274, 207;  220, 127, 145
 //   150 of 5120 points, 2^13 bins: 568, 434, 411;  570, 493, 502;  404, 249, 339
 //   one of 640 points, 2^10 bins:   72,  38,  37;   92,  58,  24;   54,  23,  16
-template <typename S, int LS>
+// Band plans, one sincospi a point and wave instead of one for every strip, the
+// whole search, H = 5, the harmonics over 10 and 80 % of the grid, likewise:
+//   300 of 3000 points, 2^13 bins: 1271, 1717, 1157;  1360, 1109, 990
+//   20 of 50000 points, 2^16 bins: 4200, 1840, 1105;  1138, 974, 763
+template <typename S, int LS, bool BAND>
 __device__ __forceinline__ void spread_cells(const double* __restrict__ t,
                                              const double* __restrict__ x,
                                              const double* __restrict__ sigma,
                                              const Moments& mo, const Geom& g,
                                              const int32_t* __restrict__ rows, int ntb, int p,
                                              int strip, cplx<S>* __restrict__ out,
-                                             CellPoints& sh, int lane) {
-  static_assert(2 << LS == 64, "a lane per cell of two strips");
+                                             CellPoints<BAND>& sh, int lane) {
+  constexpr int kStrips = spread_strips_per_wave(BAND), kRuns = kStrips / 2;
+  static_assert(kStrips << LS == 64 * kRuns, "a lane per cell of two strips");
   static_assert(kCellPoints < 512, "the search's first step");
   constexpr bool EXACT = sizeof(S) == 8;
   const double two_over_w = 2.0 / (double)g.w;
   const double beta = g.beta;
-  const double cl = (double)lane, half = 0.5 * (double)g.w;
+  const double half = 0.5 * (double)g.w;
   const int nstrip = (int)(g.L >> LS);
-  double acc[2];
+  double acc[2], acc_i[2];  // of components, or (BAND) of the wave's two runs of 64 cells
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the points take the cells' place
   // one body for both components: unrolled, its registers cost waves
 #pragma unroll 1
-  for (int c = 0; c < 2; ++c) {
+  for (int c = 0; c < (BAND ? 1 : 2); ++c) {
     const int m = g.comp_m[p][c], kind = g.comp_kind[p][c];
     const int32_t* row = rows + (int64_t)(m - 1) * ntb;
     const int lim = m ? (int)tile_limit_of(mo, g, m, LS) : 0;
-    double a = 0.0;
+    double a[kRuns], ai[kRuns];
+#pragma unroll
+    for (int h = 0; h < kRuns; ++h) a[h] = ai[h] = 0.0;
     for (int lap = 0; lap < g.laps; ++lap) {
       const int ut = strip + lap * nstrip;
       if (ut + 2 > lim) break;  // no point reaches this far
       const double base = (double)((int64_t)ut << LS);
+      const int end = ut + kStrips + 1;
       int lo = __builtin_amdgcn_readfirstlane(row[ut]);
-      const int hi = __builtin_amdgcn_readfirstlane(row[ut + 3 <= lim ? ut + 3 : lim]);
+      const int hi = __builtin_amdgcn_readfirstlane(row[end <= lim ? end : lim]);
       while (lo < hi) {
         const int n = hi - lo < kCellPoints ? hi - lo : kCellPoints;
         for (int i = lane; i < n; i += 64) {
           const PointLane pt =
-              load_point<false>(t, x, sigma, mo, g, m, kind, mo.start + lo + i, base);
+              load_point<BAND>(t, x, sigma, mo, g, m, kind, mo.start + lo + i, base);
           sh.q[i] = make_double2(pt.rel, pt.re);
+          if constexpr (BAND) sh.im[i] = pt.im;
         }
-        if (lane < kTapUnroll) sh.q[n + lane] = make_double2(1e300, 0.0);
+        if (lane < kTapUnroll) {
+          sh.q[n + lane] = make_double2(1e300, 0.0);
+          if constexpr (BAND) sh.im[n + lane] = 0.0;
+        }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
         const double2* q = sh.q;
-        int k = 0;
+#pragma unroll 1
+        for (int h = 0; h < kRuns; ++h) {
+          const double cl = (double)(lane + 64 * h);
+          double s = h ? a[kRuns - 1] : a[0], si = h ? ai[kRuns - 1] : ai[0];
+          int k = 0;
 #pragma unroll
-        for (int step = 256; step > 0; step >>= 1)
-          if (k + step <= n && q[k + step - 1].x < cl - half) k += step;
-        while (q[k].x <= cl + half) {
-          double phi[kTapUnroll], v[kTapUnroll];
+          for (int step = 256; step > 0; step >>= 1)
+            if (k + step <= n && q[k + step - 1].x < cl - half) k += step;
+          while (q[k].x <= cl + half) {
+            double phi[kTapUnroll], v[kTapUnroll], vi[kTapUnroll];
 #pragma unroll
-          for (int u = 0; u < kTapUnroll; ++u) {
-            phi[u] = es_kernel<EXACT>((cl - q[k + u].x) * two_over_w, beta);
-            v[u] = q[k + u].y;
+            for (int u = 0; u < kTapUnroll; ++u) {
+              phi[u] = es_kernel<EXACT>((cl - q[k + u].x) * two_over_w, beta);
+              v[u] = q[k + u].y;
+              if constexpr (BAND) vi[u] = sh.im[k + u];
+            }
+#pragma unroll
+            for (int u = 0; u < kTapUnroll; ++u) {
+              s = fma(phi[u], v[u], s);
+              if constexpr (BAND) si = fma(phi[u], vi[u], si);
+            }
+            k = k + kTapUnroll < n ? k + kTapUnroll : n;
           }
-#pragma unroll
-          for (int u = 0; u < kTapUnroll; ++u) a = fma(phi[u], v[u], a);
-          k = k + kTapUnroll < n ? k + kTapUnroll : n;
+          (h ? a[kRuns - 1] : a[0]) = s;
+          (h ? ai[kRuns - 1] : ai[0]) = si;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
         lo += n;
       }
     }
-    (c ? acc[1] : acc[0]) = a;
+    if constexpr (BAND) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        acc[h] = a[h];
+        acc_i[h] = ai[h];
+      }
+    } else {
+      (c ? acc[1] : acc[0]) = a[0];
+    }
   }
-  out[lane] = cmk<S>((S)acc[0], (S)acc[1]);
+  if constexpr (BAND) {
+    out[lane] = cmk<S>((S)acc[0], (S)acc_i[0]);
+    out[lane + 64] = cmk<S>((S)acc[1], (S)acc_i[1]);
+  } else {
+    out[lane] = cmk<S>((S)acc[0], (S)acc[1]);
+  }
 }
 
 // The wave's strips from `strip` on, of packed grid p of the curve mo (its table
@@ -307,8 +353,8 @@ __device__ __forceinline__ void spread_strips(const double* __restrict__ t,
       hi = mo.start + row[ut + 2];
     }
     if constexpr (DENSE) {
-      if (lap == 0 && cells_pay<EXACT>((int)(hi - lo))) {
-        spread_cells<S, LS>(t, x, sigma, mo, g, rows, ntb, p, strip, out, smem.pts, lane);
+      if (lap == 0 && cells_pay<EXACT, BAND>((int)(hi - lo))) {
+        spread_cells<S, LS, BAND>(t, x, sigma, mo, g, rows, ntb, p, strip, out, smem.pts, lane);
         return;
       }
     }

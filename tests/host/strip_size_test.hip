@@ -1,6 +1,6 @@
 // The spreading's choice of strip size (spread_table_log) on the host: strips of
-// 32 cells at any size of launch only where they can be spread by cells, which
-// band plans' never are; elsewhere the size of the launch decides.
+// 32 cells at any size of launch where they are spread by cells, from eight points
+// in 128 cells on (band plans: sixteen); elsewhere the size of the launch decides.
 #include <cstdio>
 
 #include "../../paper_0901_1913_amd/csrc/spread.hip"
@@ -13,7 +13,7 @@ int main() {
     for (int logl = 11; logl <= 26; ++logl)
       for (int P : {2, 5, 12, 24})
         for (int nc : {1, 20, 400, 4000})
-          for (int per128 : {0, 1, 3, 4, 7, 8, 30, 1000}) {  // points in 128 cells
+          for (int per128 : {0, 1, 3, 4, 7, 8, 15, 16, 30, 1000}) {  // points in 128 cells
             Geom g{};
             g.band = band;
             g.L = (int64_t)1 << logl;
@@ -21,7 +21,7 @@ int main() {
             const int64_t n = per128 * (g.L / 128);
             const int64_t waves = (g.L >> 9) * P * nc;
             const int most = per128 >= 4 ? 65536 : per128 < 1 ? 0 : 20000;
-            const bool small = (!band && per128 >= 8) || (4 * n >= g.L / 128 && waves < most);
+            const bool small = per128 >= (band ? 16 : 8) || (4 * n >= g.L / 128 && waves < most);
             const int want = small ? kStripLogMin : kStripLogMax;
             ++checked;
             if (spread_table_log(g, nc, n, n) != want) {

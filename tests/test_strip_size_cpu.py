@@ -1,7 +1,7 @@
 """Host build of the spreading's choice of strip size (csrc/spread.hip,
 spread_table_log): dense launches of any size take strips of 32 cells, spread by
-cells, except band plans, whose strips have no such form; elsewhere the number
-of waves decides."""
+cells, band plans from twice the density on; elsewhere the number of waves
+decides."""
 import os
 import shutil
 import subprocess
