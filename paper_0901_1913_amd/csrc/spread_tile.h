@@ -182,16 +182,16 @@ __device__ __forceinline__ bool cells_pay(int n) {
 // Each cell adds the same terms in the same order as in spread_strips.
 //
 // What bounds it: FP64 arithmetic where many curves fill the device, the longest
-// sequence of taps elsewhere.  Spreading of equal curves, H = 4, in us, by a
-// workgroup per tile of 1024 cells (the form before the strips), by strips alone
-// and with this, the harmonics over 7, 20 and 70 % of the grid:
+// sequence of taps elsewhere.  Spreading of equal curves, H = 4, in us, the
+// harmonics over 7, 20 and 70 % of the grid, three figures each: by a workgroup
+// per tile of 1024 cells (the form before the strips); by strips alone; with this:
 //   400 of 640 points, 2^10 bins:  201, 130, 172;  357, 274, 207;  220, 127, 145
 //   150 of 5120 points, 2^13 bins: 568, 434, 411;  570, 493, 502;  404, 249, 339
 //   one of 640 points, 2^10 bins:   72,  38,  37;   92,  58,  24;   54,  23,  16
 // Band plans, one sincospi a point and wave instead of one for every strip, the
-// whole search, H = 5, the harmonics over 10 and 80 % of the grid, likewise:
-//   300 of 3000 points, 2^13 bins: 1271, 1717, 1157;  1360, 1109, 990
-//   20 of 50000 points, 2^16 bins: 4200, 1840, 1105;  1138, 974, 763
+// whole search, H = 5, over 10 and 80 %:
+//   300 of 3000 points, 2^13 bins: 1271, 1360;  1717, 1109;  1157, 990
+//   20 of 50000 points, 2^16 bins: 4200, 1138;  1840, 974;   1105, 763
 template <typename S, int LS, bool BAND>
 __device__ __forceinline__ void spread_cells(const double* __restrict__ t,
                                              const double* __restrict__ x,
